@@ -217,8 +217,10 @@ ql_status ql_quantize_activations(const float *X, int64_t m, int64_t cols, const
  * n layers do not fit one launch (or projection layers at B > 1).  Same
  * results, bit for bit, as n calls of the one-layer path. */
 size_t ql_lstm_stack_workspace(const ql_lstm_layer *layers, int32_t n, int64_t T, int64_t B);
-/* How many of the first n layers one launch holds on the current device (the
- * grouping ql_acoustic_model_forward uses); 1 when they cannot share one.
+/* How many of the first n layers one launch holds together with the whole
+ * batch on the current device; 1 when they cannot share one.
+ * (ql_acoustic_model_forward may run more layers a launch than this, by
+ * splitting the batch over several launches instead.)
  * Layers that all have a projection (H, P, in <= 512) share launches at batch 1:
  * ql_acoustic_model_forward and ql_lstm_stack_forward run them as a wavefront
  * too. */
@@ -413,10 +415,12 @@ ql_status ql_debug_set_wait_bound(int32_t polls);
 int32_t ql_debug_recurrence_layout(const ql_lstm_layer *L, int64_t B);
 /* Test hook: which layout the first wavefront launch over the n stacked
  * layers (no projection) runs in for T frames at batch B on the current
- * device -- 1: one persistent launch over the whole chip with one XCD per
- * layer (batch 16 to 64, 2 to 8 layers, widths up to 512, 256 CUs), 0: any
- * other path (including none); -1 for an invalid layer, n < 1, T < 0 or
- * B < 0.  The layers are read, never written. */
+ * device -- 1: one persistent launch over the whole chip with the row groups of
+ * every layer on XCDs of their own, at the batches ql_lstm_stack_forward
+ * always accepts for it (16 to 64; 2 to 8 layers, widths up to 512, 256 CUs),
+ * 0: anything else (including none, and the same kernel at other batches);
+ * -1 for an invalid layer, n < 1, T < 0 or B < 0.  The layers are read, never
+ * written. */
 int32_t ql_debug_stack_layout(const ql_lstm_layer *layers, int32_t n, int64_t T, int64_t B);
 /* Elementwise gate functions on device arrays (fn 0 = e^x, 1 = sigmoid,
  * 2 = tanh, 3 = the reciprocal 1 / d that sigmoid applies to d = 1 + e^-x,

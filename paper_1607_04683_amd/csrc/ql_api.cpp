@@ -561,7 +561,7 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   int per_launch = 1;
   if (stack) {
     const int64_t in1 = M->nlayers > 1 ? M->layers[1].in : M->layers[0].in;
-    per_launch = stack_layers_per_launch(M->nlayers, T, B, maxH, M->layers[0].in, in1);
+    per_launch = stack_layers_routed(M->nlayers, T, B, maxH, M->layers[0].in, in1);
   } else if (pst) {
     per_launch = pstack_per_launch(M->layers, M->nlayers, T, B);
   }
@@ -971,6 +971,7 @@ ql_status ql_lstm_stack_forward(const ql_lstm_layer *layers, int32_t n, const ql
                           k);
     if (k == n - 1 && h_last && !sa.L[k].h) sa.L[k].h = h_last;
   }
+  if (!stack_fits_one_launch(sa)) return QL_EUNSUPPORTED;
   bool unsupported = false;
   if (launch_stack(sa, s, &unsupported) != hipSuccess) return QL_EHIP;
   if (unsupported) return QL_EUNSUPPORTED;

@@ -182,17 +182,27 @@ hipError_t launch_pstack(const PStackArgs &a, hipStream_t s, bool *unsupported);
 int pstack_layers_per_launch(const PStackArgs &a);
 
 hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported);
-// Batch 16 to 64 on the whole chip (ql_xstack.hip): one XCD per layer.  *done
-// false when the shapes or the device do not fit that layout (nothing
-// launched).
+// The same on the whole chip as independent row groups of 16 workgroups each
+// (ql_xstack.hip), over as many launches as the batch needs; ws_bytes of a.ws
+// may be used.  *done false when the shapes or the device do not fit that
+// layout (nothing launched).
 size_t xstack_ws(int nl);
-bool xstack_applies(const StackArgs &a, int cus, int lds_max);
-hipError_t launch_xstack(const StackArgs &a, int cus, int lds_max, bool taps, hipStream_t s,
-                         bool *done);
-// 1 when launch_stack would run a in that layout on the current device, else 0.
+bool xstack_shapes(int nl, int64_t B, int64_t H, int64_t in0, int64_t in1, size_t ws_bytes, int cus,
+                   int lds_max);
+bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max);
+hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,
+                         hipStream_t s, bool *done);
+// 1 when launch_stack would run a in that layout at batch 16 to 64 on the
+// current device, else 0.
 int stack_layout(const StackArgs &a);
 // How many layers of such a stack fit one launch (1: none, use the one-layer path).
 int stack_layers_per_launch(int n, int64_t T, int64_t B, int64_t H, int64_t in0, int64_t in1);
+// Whether all of a's layers and rows go into one launch (what
+// ql_lstm_stack_forward accepts).
+bool stack_fits_one_launch(const StackArgs &a);
+// How many layers launch_stack takes at once: as above, or all of them where
+// the row-group layout splits the batch over launches instead of the layers.
+int stack_layers_routed(int n, int64_t T, int64_t B, int64_t H, int64_t in0, int64_t in1);
 
 // ---- unquantized fp32 model (ql_f32.hip)
 // C[m][n] = sum_k A[m][k] B[n][k] (+ bias[n]); bias nullable.

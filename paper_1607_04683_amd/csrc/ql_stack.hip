@@ -950,7 +950,10 @@ int stack_layout(const StackArgs &a) {
     (void)hipGetLastError();
     return 0;
   }
-  return xstack_applies(a, cus, lds_max) ? 1 : 0;
+  return a.B >= 16 && a.B <= 64 && a.nl >= 2 &&
+                 xstack_applies(a, stack_ws(a.nl, a.T, a.B, a.H), cus, lds_max)
+             ? 1
+             : 0;
 }
 
 hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
@@ -971,9 +974,9 @@ hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
-  // batch 16 to 64 on the whole chip: one XCD per layer
+  // two or more batch rows on the whole chip: row groups on XCDs of their own
   bool done = false;
-  e = launch_xstack(a, cus, lds_max, tp, s, &done);
+  if (a.B > 1) e = launch_xstack(a, stack_ws(a.nl, a.T, a.B, a.H), cus, lds_max, tp, s, &done);
   if (e != hipSuccess || done) return e;
   StackTiling tl;
   if (!plan_stack(a, cus, lds_max, &tl)) {
@@ -1000,6 +1003,30 @@ hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
   void *kargs[] = {&args, &tl};
   return hipLaunchCooperativeKernel(reinterpret_cast<void *>(kern), dim3(tl.grid),
                                     dim3(kStackThreads), kargs, (unsigned)tl.lds_bytes, s);
+}
+
+bool stack_fits_one_launch(const StackArgs &a) {
+  if (stack_layout(a)) return true;
+  int dev = 0, cus = 0, lds_max = 0;
+  StackTiling tl;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess)
+    return a.H <= 512 && plan_stack(a, cus, lds_max, &tl);
+  (void)hipGetLastError();
+  return true;  // launch_stack reports the error
+}
+
+int stack_layers_routed(int n, int64_t T, int64_t B, int64_t H, int64_t in0, int64_t in1) {
+  int dev = 0, cus = 0, lds_max = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) {
+    const int nl = std::min(n, kMaxStack);
+    if (B > 1 && xstack_shapes(nl, B, H, in0, in1, stack_ws(nl, T, B, H), cus, lds_max)) return nl;
+  }
+  (void)hipGetLastError();
+  return stack_layers_per_launch(n, T, B, H, in0, in1);
 }
 
 // Layers per launch for a stack of n layers of width H at batch B: the most

@@ -1,17 +1,27 @@
-// ql_xstack.hip -- stacked LSTM layers without a projection (Section 4) at
-// batch 16 .. 64 in one persistent launch over the whole chip, one XCD per
-// layer, run as a wavefront: layer l works on frame t while layer l-1 is
-// already further on.
+// ql_xstack.hip -- stacked LSTM layers without a projection (Section 4) in
+// persistent launches over the whole chip, run as a wavefront: layer l works
+// on frame t while layer l-1 is already further on.
 //
-// XCD l runs layer l for the whole sequence and the whole batch; its 32
-// workgroups (one per CU; each reads its XCC_ID and takes the next free slot
-// s of its XCD) are 2 row groups (half of the batch each) x 16 cell tiles (32
-// cells each).  Every hand-off inside a layer stays in that XCD's L2: plain
-// stores, device-coherent loads that find them there.  A tile keeps the 128
-// gate rows of its cells of both W_x' and W_h' in registers as MFMA
-// fragments, four cells (their gates i f g o adjacent) per 16-row block, so
-// an MFMA result gives a lane the four gate sums of one (cell, row) pair, and
-// c stays in that lane's registers.  A step t, for the tile's rows:
+// The unit of work is a row group of one layer: up to 32 batch rows over the
+// whole sequence, on 16 workgroups of one XCD (one per CU; each reads its
+// XCC_ID and takes the next free slot of its XCD), 32 cells each.  The chip
+// holds 16 units, so n layers take floor(16 / n) row groups a launch (5
+// layers: 96 rows), and larger batches several launches.  Every hand-off
+// inside a unit stays in that XCD's L2: plain stores, device-coherent loads
+// that find them there.  What bounds it is the latency of two such hand-offs
+// and the phases between them, not the rows: a frame through 5 x 500 cells
+// takes 4.9-5.1 us in groups of up to 16 rows and 7.0-7.3 us in groups of up
+// to 32 (200 frames, start-up included), so the batch is cut into groups of
+// 16 while the chip holds them and of 32 beyond.  Before, one XCD per layer
+// with two row groups served batch 16 to 64 only, and k_stack the others, us a
+// frame before and now: 6 rows 23.7 and 4.9, 48 rows 7.0 and 5.1, 80 rows
+// 16.4 and 7.2, 150 rows 28.8 and 14.0, 192 rows 57 and 14.2.
+//
+// A tile keeps the 128 gate rows of its cells of both W_x' and W_h' in
+// registers as MFMA fragments, four cells (their gates i f g o adjacent) per
+// 16-row block, so an MFMA result gives a lane the four gate sums of one
+// (cell, row) pair, and c stays in that lane's registers.  A step t, for the
+// tile's rows:
 //   1. the codes of x_t (the launch's input, or the codes layer l-1 made of
 //      its h_t, published across XCDs with an arrival counter) and their
 //      product with W_x', recovered (eq. 1 / eq. 3) plus the bias, exactly
@@ -49,17 +59,19 @@ constexpr int kXsThreads = 512;
 constexpr int kXsWaves = kXsThreads / 64;
 constexpr int kXsXcds = 8;      // XCDs of the MI355X, each with its own L2
 constexpr int kXsSlots = 32;    // CUs (workgroups) of one XCD
-constexpr int kXsGroups = 2;    // row groups of a layer
-constexpr int kXsTiles = 16;    // cell tiles of a row group
+constexpr int kXsTiles = 16;    // cell tiles (workgroups) of a row group
+constexpr int kXsUnits = kXsXcds * kXsSlots / kXsTiles;  // row groups a launch can hold
 constexpr int kXsCells = 32;    // cells of a tile: one 4-cell block per wave
 constexpr int kXsMaxW = 512;    // widths (cells, input) the layout is sized for
 constexpr int kXsSlotBytes = kXsXcds * 64;
-constexpr int kXsCounterBytes = kMaxStack * 2 * kXsGroups * 64;  // [layer][parity][group]
+constexpr int kXsCounterBytes = kXsUnits * 2 * 64;  // [unit][parity]
 
 struct XsTiling {
-  int rows;          // batch rows per row group (the second may hold fewer)
+  int ng;            // row groups per layer
+  int rows;          // batch rows per row group (the last may hold fewer)
+  int64_t r0, r1;    // batch rows [r0, r1) of this launch
   size_t lds_bytes;  // (host) dynamic LDS of the instance
-  int64_t xwords;    // (host) exchange words per layer
+  int64_t xwords;    // (host) exchange words per unit
 };
 
 // LDS and exchange layout of an instance (rows per group up to 16 NT).
@@ -88,7 +100,7 @@ struct XsLay {
   static constexpr int64_t e2c = e1 + (int64_t)bX * kXsTiles * 2;
   static constexpr int64_t e2s = e2c + (int64_t)bX * kXsTiles * uw;
   static constexpr int64_t gwords = (e2s + (int64_t)bX * kXsTiles + 31) / 32 * 32;
-  static constexpr int64_t lwords = 2 * kXsGroups * gwords;  // a layer: 2 parities x 2 groups
+  static constexpr int64_t uwords = 2 * gwords;  // a unit: 2 parities
 };
 
 struct XsKArgs {
@@ -103,24 +115,24 @@ typedef const __attribute__((address_space(4))) XsKArgs *XsKArgPtr;
 // and output addresses) is held in vector registers instead, so that no
 // scalar reload sits on the step's chain.
 #define XS_SCALARS(a, tl, role)                                                                 \
-  const int l = (role) / kXsSlots, s = (role) % kXsSlots;                                      \
-  const int g = s / kXsTiles, ct = s % kXsTiles;                                               \
+  const int unit = (role) / kXsTiles, ct = (role) % kXsTiles;                                  \
+  const int l = unit / tl.ng, g = unit % tl.ng;                                                \
   auto &Ly = a.L[l];                                                                           \
   const int64_t T = a.T, B = a.B, H = a.H, IN = Ly.in;                                         \
   int *flag = reinterpret_cast<int *>(a.ws) + kHdrFlag;                                        \
-  const int64_t b0 = (int64_t)g * tl.rows;                                                     \
-  const int nb = (int)std::min<int64_t>((int64_t)tl.rows, B - b0);                             \
+  const int64_t b0 = tl.r0 + (int64_t)g * tl.rows;                                             \
+  const int nb = (int)std::min<int64_t>((int64_t)tl.rows, tl.r1 - b0);                         \
   const int64_t j0 = (int64_t)ct * u;                                                          \
   const int ldX = (int)((IN + 63) / 64 * 64), ldH = (int)((H + 63) / 64 * 64);                 \
   unsigned *cnt0 = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes +     \
                                                 kXsSlotBytes);                                 \
   auto ctr = [&](int layer, int64_t par, int grp) {                                            \
-    return cnt0 + ((layer * 2 + (int)par) * kXsGroups + grp) * 16;                             \
+    return cnt0 + ((layer * tl.ng + grp) * 2 + (int)par) * 16;                                 \
   };                                                                                           \
   uint64_t *X = reinterpret_cast<uint64_t *>(static_cast<char *>(a.ws) + kHeaderBytes +        \
                                              kXsSlotBytes + kXsCounterBytes) +                 \
-                (int64_t)l * L::lwords;                                                        \
-  auto E = [&](int64_t tt_) { return X + ((tt_ & 1) * kXsGroups + g) * L::gwords; };          \
+                (int64_t)unit * L::uwords;                                                     \
+  auto E = [&](int64_t tt_) { return X + (tt_ & 1) * L::gwords; };                             \
   (void)T, (void)flag, (void)ldX, (void)ldH, (void)ctr, (void)E, (void)IN
 
 template <int NT, bool TP>
@@ -136,10 +148,13 @@ __global__ __launch_bounds__(kXsThreads) void k_xstack(StackArgs a, XsTiling tl)
     unsigned *slots = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
     s_role = -1;
     s_abort = 0;
-    if (xcc < a.nl) {
+    if (xcc < kXsXcds) {
       const unsigned k = __hip_atomic_fetch_add(slots + xcc * 16, 1u, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
-      if (k < (unsigned)kXsSlots) s_role = xcc * kXsSlots + (int)k;
+      // units 0 .. 7 on an XCD of their own each, then the second halves
+      const int unit = (int)(k / kXsTiles) * kXsXcds + xcc;
+      if (k < (unsigned)kXsSlots && unit < a.nl * tl.ng)
+        s_role = unit * kXsTiles + (int)(k % kXsTiles);
     }
   }
   __syncthreads();
@@ -266,10 +281,10 @@ __global__ __launch_bounds__(kXsThreads) void k_xstack(StackArgs a, XsTiling tl)
   int64_t xrow8 = 8 * Ly.xin.ld, xstep = B * Ly.xin.ld, xB = B;
   int xin_k = (int)IN;
   asm volatile("" : "+v"(xrow8), "+v"(xstep), "+v"(xB), "+v"(xin_k));
-  const unsigned *cprev = l > 0 ? ctr(l - 1, 0, g) : nullptr;  // parity 1: + kXsGroups * 16
+  const unsigned *cprev = l > 0 ? ctr(l - 1, 0, g) : nullptr;  // parity 1: + 16
   auto load_x = [&](int64_t tx, unsigned seen) {
     if (cprev) {
-      const unsigned *c = cprev + (tx & 1) * (kXsGroups * 16);
+      const unsigned *c = cprev + (tx & 1) * 16;
       const unsigned target = (unsigned)((tx >> 1) + 1) * kXsTiles;
       long it = 0;
       while (seen < target) {
@@ -680,23 +695,60 @@ __global__ __launch_bounds__(kXsThreads) void k_xstack(StackArgs a, XsTiling tl)
 }
 
 // ------------------------------------------------------------------ host side
-size_t xstack_ws(int nl) {
-  return kHeaderBytes + kXsSlotBytes + kXsCounterBytes + (size_t)nl * XsLay<2>::lwords * 8;
+static size_t unit_bytes(int nt) {
+  return (size_t)(nt == 1 ? XsLay<1>::uwords : XsLay<2>::uwords) * 8;
+}
+constexpr size_t kXsHead = kHeaderBytes + kXsSlotBytes + kXsCounterBytes;
+
+size_t xstack_ws(int nl) { return kXsHead + (size_t)nl * 2 * unit_bytes(2); }
+
+bool xstack_shapes(int nl, int64_t B, int64_t H, int64_t in0, int64_t in1, size_t ws_bytes, int cus,
+                   int lds_max) {
+  if (nl < 1 || nl > kMaxStack) return false;
+  StackArgs a{};
+  a.nl = nl;
+  a.B = B;
+  a.H = H;
+  for (int l = 0; l < nl; ++l) {
+    a.L[l].in = l == 0 ? in0 : in1;
+    a.L[l].Wx.ld = round_up(a.L[l].in, 64);
+    a.L[l].Wh.ld = a.L[l].out.ld = round_up(H, 64);
+  }
+  return xstack_applies(a, ws_bytes, cus, lds_max);
 }
 
-static bool plan_xstack(const StackArgs &a, int cus, int lds_max, XsTiling *out) {
-  if (cus != kXsXcds * kXsSlots || a.nl < 2 || a.nl > kXsXcds) return false;
-  if (a.B < 16 || a.B > kXsGroups * 32 || a.H > kXsTiles * kXsCells) return false;
-  XsTiling tl{};
-  tl.rows = (int)((a.B + kXsGroups - 1) / kXsGroups);
+// The rows from r0 on that one launch takes.  Row groups of up to 16 rows when
+// the chip (and the scratch) holds enough of them for the whole batch: their
+// step is 4.9-5.1 us against 7.0-7.3 us with up to 32 (more, smaller groups
+// than that are no faster: 6 rows in one, two or three groups 4.95, 4.90,
+// 5.01).  Otherwise groups of up to 32 rows, and as few launches, of equal
+// size, as the batch needs.
+static bool plan_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, int64_t r0,
+                        XsTiling *out) {
+  if (cus != kXsXcds * kXsSlots || a.nl < 1 || a.nl > kXsXcds) return false;
+  if (a.B < 1 || a.H > kXsTiles * kXsCells || ws_bytes < kXsHead) return false;
   const int64_t ldH = round_up(a.H, 64);
   for (int l = 0; l < a.nl; ++l) {
     const StackLayer &L = a.L[l];
     if (L.in > kXsMaxW || L.Wx.ld < round_up(L.in, 64) || L.Wh.ld < ldH) return false;
     if (L.out.ld < ldH || L.out.ld % 4) return false;
   }
-  tl.lds_bytes = tl.rows <= 16 ? XsLay<1>::bytes : XsLay<2>::bytes;
-  tl.xwords = XsLay<2>::lwords;
+  auto groups = [&](int nt) {
+    const size_t fit = (ws_bytes - kXsHead) / (a.nl * unit_bytes(nt));
+    return (int64_t)std::min<size_t>(kXsUnits / a.nl, fit);
+  };
+  const int nt = a.B <= 16 * groups(1) ? 1 : 2;
+  const int64_t most = 16 * nt * groups(nt);  // rows of a launch
+  if (most < 1) return false;
+  const int64_t launches = (a.B + most - 1) / most, chunk = (a.B + launches - 1) / launches;
+  XsTiling tl{};
+  tl.r0 = r0;
+  tl.r1 = std::min(a.B, r0 + chunk);
+  const int64_t n = tl.r1 - tl.r0;
+  tl.ng = (int)((n + 16 * nt - 1) / (16 * nt));
+  tl.rows = (int)((n + tl.ng - 1) / tl.ng);
+  tl.lds_bytes = nt == 1 ? XsLay<1>::bytes : XsLay<2>::bytes;
+  tl.xwords = (int64_t)unit_bytes(nt) / 8;
   if (tl.lds_bytes + 64 > (size_t)lds_max) return false;
   *out = tl;
   return true;
@@ -704,33 +756,40 @@ static bool plan_xstack(const StackArgs &a, int cus, int lds_max, XsTiling *out)
 
 using XsKernel = void (*)(StackArgs, XsTiling);
 
-bool xstack_applies(const StackArgs &a, int cus, int lds_max) {
+bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max) {
   XsTiling tl;
-  return plan_xstack(a, cus, lds_max, &tl);
+  return plan_xstack(a, ws_bytes, cus, lds_max, 0, &tl);
 }
 
-hipError_t launch_xstack(const StackArgs &a, int cus, int lds_max, bool taps, hipStream_t s,
-                         bool *done) {
+hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,
+                         hipStream_t s, bool *done) {
   *done = false;
-  XsTiling tl;
-  if (!plan_xstack(a, cus, lds_max, &tl)) return hipSuccess;
-  XsKernel kern = tl.rows <= 16 ? (taps ? k_xstack<1, true> : k_xstack<1, false>)
-                                : (taps ? k_xstack<2, true> : k_xstack<2, false>);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)tl.lds_bytes);
-  if (e != hipSuccess) return e;
-  int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kXsThreads, tl.lds_bytes);
-  if (e != hipSuccess) return e;
-  if (per_cu < 1) return hipSuccess;
-  e = clear_exchange(a.ws, (kXsSlotBytes + kXsCounterBytes) / 8 + (int64_t)a.nl * tl.xwords, s);
-  if (e != hipSuccess) return e;
-  StackArgs args = a;
-  void *kargs[] = {&args, &tl};
-  e = hipLaunchCooperativeKernel(reinterpret_cast<void *>(kern), dim3(cus), dim3(kXsThreads), kargs,
-                                 (unsigned)tl.lds_bytes, s);
-  if (e == hipSuccess) *done = true;
-  return e;
+  for (int64_t r0 = 0; r0 < a.B;) {
+    XsTiling tl;
+    if (!plan_xstack(a, ws_bytes, cus, lds_max, r0, &tl)) return hipSuccess;
+    const bool one = tl.lds_bytes == XsLay<1>::bytes;
+    XsKernel kern = one ? (taps ? k_xstack<1, true> : k_xstack<1, false>)
+                        : (taps ? k_xstack<2, true> : k_xstack<2, false>);
+    hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)tl.lds_bytes);
+    if (e != hipSuccess) return e;
+    int per_cu = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kXsThreads, tl.lds_bytes);
+    if (e != hipSuccess) return e;
+    if (per_cu < 1) return hipSuccess;
+    e = clear_exchange(a.ws, (kXsSlotBytes + kXsCounterBytes) / 8 + (int64_t)a.nl * tl.ng * tl.xwords,
+                       s);
+    if (e != hipSuccess) return e;
+    StackArgs args = a;
+    void *kargs[] = {&args, &tl};
+    e = hipLaunchCooperativeKernel(reinterpret_cast<void *>(kern), dim3(cus), dim3(kXsThreads),
+                                   kargs, (unsigned)tl.lds_bytes, s);
+    if (e != hipSuccess) return e;
+    r0 = tl.r1;
+  }
+  *done = true;
+  return hipSuccess;
 }
 
 hipError_t set_wait_bound_xstack(int polls) { return set_wait_bound_here(polls); }

@@ -776,8 +776,8 @@ def recurrence_layout(L: Layer, B: int) -> int:
 
 
 def stack_layout(M: Model, T: int, B: int) -> int:
-    """1 when the first wavefront launch over M's layers runs with one XCD per
-    layer (batch 16 to 64 on the whole chip), else 0."""
+    """1 when the first wavefront launch over M's layers runs as row groups on
+    XCDs of their own at batch 16 to 64 (the whole chip), else 0."""
     arr = (CLayer * len(M.layers))(*[L.cstruct() for L in M.layers])
     return int(load().ql_debug_stack_layout(arr, len(M.layers), T, B))
 

@@ -77,3 +77,57 @@ def test_xcd_stack_repeats_bit_for_bit(ql):
         for l in range(5):
             assert torch.equal(got["layers"][l]["h_codes"], ref["layers"][l]["h_codes"]), l
         assert torch.equal(got["post"], ref["post"])
+
+
+# Row groups: 16 of them share the chip, up to 16 rows each, up to 32 when the
+# batch needs it, several launches beyond.  Batches at the edges of these.
+GROUP_CASES = [
+    (2, 40, 48, 6, 2),       # the smallest batch
+    (5, 40, 36, 5, 15),      # one group per layer, one row short
+    (8, 24, 64, 5, 33),      # 2 groups of 32 rows at most: 17 + 16
+    (3, 24, 100, 4, 65),     # 5 groups of 13 rows
+    (5, 40, 48, 4, 49),      # one row more than 3 groups of 16 hold
+    (5, 40, 500, 3, 97),     # one row more than a launch holds: 49 + 48
+    (4, 512, 512, 2, 128),   # a full launch at the widest
+    (3, 320, 260, 3, 190),   # two launches of 3 groups of 32
+    (5, 24, 16, 3, 150),     # narrow cells: the scratch holds fewer groups
+    (9, 24, 32, 3, 20),      # more layers than one launch holds: 5 + 4
+]
+
+
+@pytest.mark.parametrize("layers,n_in,H,T,B", GROUP_CASES)
+def test_row_groups_equal_oracle(ql, orc, layers, n_in, H, T, B):
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(n_in, H, layers, states=40, seed=layers * 1000 + H + B)
+    x = np.random.default_rng(B + H).standard_normal((T, B, n_in)).astype(np.float32)
+    M = ql.quantize_model(w)
+    g = ql.acoustic_model_forward(M, torch.from_numpy(x).cuda(), taps=True)
+    o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
+    assert_model_taps(g, o, None, names=ql.TAP_NAMES)
+
+
+@pytest.mark.parametrize("B", [3, 100])
+def test_row_groups_carry_state(ql, B):
+    """Chunks of a sequence with the state carried give the whole call's bits."""
+    from paper_1607_04683_amd.workloads import random_model
+    M = ql.quantize_model(random_model(40, 100, 5, states=32, seed=B))
+    x = torch.randn(9, B, 40, device="cuda")
+    whole = ql.acoustic_model_forward(M, x)["post"]
+    state, parts = None, []
+    for a, b in [(0, 1), (1, 5), (5, 9)]:
+        out = ql.empty_state(M, B)
+        parts.append(ql.acoustic_model_forward(M, x[a:b].contiguous(), state_in=state,
+                                               state_out=out)["post"])
+        state = out
+    assert torch.equal(torch.cat(parts), whole)
+
+
+def test_stack_forward_still_takes_one_launch_only(ql):
+    """ql_lstm_stack_forward runs its layers and rows in one launch or says
+    that it cannot; only the model forward splits the batch."""
+    from paper_1607_04683_amd.workloads import random_model
+    M = ql.quantize_model(random_model(40, 500, 5, states=32, seed=1))
+    x = torch.randn(2, 150, 40, device="cuda")
+    assert ql.stack_layers_per_launch(M, 2, 150) < 5
+    with pytest.raises(ql.QLError, match="not supported"):
+        ql.lstm_stack_forward(M.layers, ql.quantize_activations(x.reshape(300, 40)), 2, 150)
