@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -213,9 +214,7 @@ const char *ql_status_str(ql_status s) {
 }
 
 size_t ql_quantize_workspace(int64_t rows, int64_t cols, int32_t nblocks) {
-  (void)rows;
-  (void)cols;
-  return set_quantize_ws(nblocks > 0 ? nblocks : 1);
+  return set_quantize_ws(rows > 0 ? rows : 0, cols > 0 ? cols : 0, nblocks > 0 ? nblocks : 1);
 }
 
 ql_status ql_quantize(const float *src, int64_t rows, int64_t cols, int32_t nblocks,
@@ -227,7 +226,7 @@ ql_status ql_quantize(const float *src, int64_t rows, int64_t cols, int32_t nblo
   if (dst->rows != rows || dst->cols != cols || dst->nblocks != nblocks) return QL_ESHAPE;
   if (dst->ld < cols || dst->ld % 64 != 0) return QL_ESHAPE;
   if (!ws || ws_bytes < ql_quantize_workspace(rows, cols, nblocks)) return QL_EWORKSPACE;
-  return from_hip(launch_set_quantize(src, cols, rows, cols, nblocks, dst->codes, dst->ld,
+  return from_hip(launch_set_quantize(src, rows, cols, nblocks, dst->codes, dst->ld,
                                       dst->range, dst->zero, dst->inv_q, dst->row_sums, nullptr,
                                       nullptr, ws, as_stream(stream)));
 }
@@ -246,7 +245,7 @@ size_t ql_quantized_matmul_workspace(int64_t m, int64_t rows, int64_t cols) {
   (void)rows;
   Carve c(nullptr);
   take_act(c, m, cols);
-  c.take<char>(set_quantize_ws(1));
+  c.take<char>(set_quantize_ws(m, cols, 1));
   return c.off;
 }
 
@@ -263,12 +262,12 @@ ql_status ql_quantized_matmul(const ql_qmatrix *W, const float *X, int64_t m, ql
   hipStream_t s = as_stream(stream);
   Carve c(ws);
   ActBuf x = take_act(c, m, W->cols);
-  void *qws = c.take<char>(set_quantize_ws(1));
+  void *qws = c.take<char>(set_quantize_ws(m, W->cols, 1));
   hipError_t e;
   if (g == QL_ACT_PER_ROW)
     e = launch_quantize_rows(X, W->cols, m, W->cols, x.codes, x.ld, x.zero, x.inv_q, x.sums, s);
   else
-    e = launch_set_quantize(X, W->cols, m, W->cols, 1, x.codes, x.ld, nullptr, nullptr, nullptr,
+    e = launch_set_quantize(X, m, W->cols, 1, x.codes, x.ld, nullptr, nullptr, nullptr,
                             x.sums, x.zero, x.inv_q, qws, s);
   if (e != hipSuccess) return QL_EHIP;
   return from_hip(launch_gemm_recover(x.rows(), weight(*W), m, W->rows, W->cols, bias, Y, acc, s));
@@ -1147,7 +1146,12 @@ TrainWs carve_train(Carve &c, const ql_train_model &M, int64_t T, int64_t B, int
   }
   const int64_t HL = M.layers[M.nlayers - 1].hidden;
   if (qout) qcopy(w.qy, M.states, HL, 1);
-  w.qws = c.take<char>(set_quantize_ws(gb));
+  size_t qws = qout ? set_quantize_ws(M.states, HL, 1) : 0;
+  for (int l = 0; l < M.nlayers; ++l) {
+    const int64_t H = M.layers[l].hidden;
+    qws = std::max({qws, set_quantize_ws(4 * H, M.layers[l].in, gb), set_quantize_ws(4 * H, H, gb)});
+  }
+  w.qws = c.take<char>(qws);
   for (int l = 0; l < M.nlayers; ++l) {
     const int64_t H = M.layers[l].hidden;
     w.gates[l] = c.take<float>((size_t)(N * 4 * H));
@@ -1224,15 +1228,15 @@ ql_status ql_train_step(const ql_train_model *M, const float *feats, const int32
   for (int l = 0; l < NL; ++l) {
     const ql_train_layer &L = M->layers[l];
     const int64_t H = L.hidden;
-    if (launch_set_quantize(L.Wx, L.in, 4 * H, L.in, gate_blocks, w.qx[l].codes,
+    if (launch_set_quantize(L.Wx, 4 * H, L.in, gate_blocks, w.qx[l].codes,
                             round_up(L.in, 64), w.qx[l].range, w.qx[l].zero, w.qx[l].inv_q,
                             w.qx[l].row_sums, nullptr, nullptr, w.qws, s) != hipSuccess ||
-        launch_set_quantize(L.Wh, H, 4 * H, H, gate_blocks, w.qh[l].codes, round_up(H, 64),
+        launch_set_quantize(L.Wh, 4 * H, H, gate_blocks, w.qh[l].codes, round_up(H, 64),
                             w.qh[l].range, w.qh[l].zero, w.qh[l].inv_q, w.qh[l].row_sums,
                             nullptr, nullptr, w.qws, s) != hipSuccess)
       return QL_EHIP;
   }
-  if (qout && launch_set_quantize(M->Wy, HL, S, HL, 1, w.qy.codes, round_up(HL, 64), w.qy.range,
+  if (qout && launch_set_quantize(M->Wy, S, HL, 1, w.qy.codes, round_up(HL, 64), w.qy.range,
                                   w.qy.zero, w.qy.inv_q, w.qy.row_sums, nullptr, nullptr, w.qws,
                                   s) != hipSuccess)
     return QL_EHIP;

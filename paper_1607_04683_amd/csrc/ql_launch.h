@@ -6,7 +6,7 @@
 
 namespace ql {
 
-constexpr int kSetParts = 128;  // partial min/max blocks per quantized set
+constexpr int kSetParts = 512;  // partial min/max blocks per quantized set, at most
 
 inline size_t align_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 inline int64_t round_up(int64_t n, int64_t a) { return (n + a - 1) / a * a; }
@@ -15,14 +15,14 @@ inline int64_t round_up(int64_t n, int64_t a) { return (n + a - 1) / a * a; }
 hipError_t launch_quantize_rows(const float *X, int64_t ldx, int64_t m, int64_t K, int8_t *codes,
                                 int64_t ld, int32_t *zero, float *inv_q, int32_t *sums,
                                 hipStream_t s);
-size_t set_quantize_ws(int nsets);
+size_t set_quantize_ws(int64_t rows, int64_t cols, int nsets);
 hipError_t launch_quantize_stacked(const float *frames, int64_t B, int dim, int stack, int skip,
                                    int64_t T, int8_t *codes, int64_t ld, int32_t *zero,
                                    float *inv_q, int32_t *sums, hipStream_t s);
-hipError_t launch_set_quantize(const float *X, int64_t ldx, int64_t rows, int64_t cols,
-                               int nsets, int8_t *codes, int64_t ld, double *range,
-                               int32_t *zero, float *inv_q, int32_t *row_sums,
-                               int32_t *row_zero, float *row_inv_q, void *ws, hipStream_t s);
+hipError_t launch_set_quantize(const float *X, int64_t rows, int64_t cols, int nsets, int8_t *codes,
+                               int64_t ld, double *range, int32_t *zero, float *inv_q,
+                               int32_t *row_sums, int32_t *row_zero, float *row_inv_q, void *ws,
+                               hipStream_t s);
 hipError_t launch_dequantize(const int8_t *codes, int64_t ld, int64_t rows, int64_t cols,
                              int nblocks, const int32_t *zero, const float *inv_q, float *dst,
                              hipStream_t s);

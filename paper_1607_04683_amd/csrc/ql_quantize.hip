@@ -9,12 +9,35 @@
 //    every third stacked frame presented), so the stacked copy is never written.
 //  * k_set_*: quantization of larger sets (a weight matrix or one of its gate
 //    blocks; a whole activation tensor): partial min/max over many blocks,
-//    a finalize step, then the row encoder.
+//    then the row encoder; one block per set for small ones.
 //  * k_dequantize: recovery of eq. 3.
 #include "ql_device.h"
 #include "ql_launch.h"
 
+#include <algorithm>
+
 namespace ql {
+
+constexpr int kEncodeRows = 16;  // rows of one block of k_set_encode
+
+// min and max over the block (up to 16 waves), in every thread.
+__device__ __forceinline__ float2 block_minmax(float lo, float hi) {
+  __shared__ float slo[16], shi[16];
+  const int nw = blockDim.x >> 6;
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  if ((threadIdx.x & 63) == 0) {
+    slo[threadIdx.x >> 6] = lo;
+    shi[threadIdx.x >> 6] = hi;
+  }
+  __syncthreads();
+  lo = slo[0], hi = shi[0];
+  for (int w = 1; w < nw; ++w) {
+    lo = fminf(lo, slo[w]);
+    hi = fmaxf(hi, shi[w]);
+  }
+  return make_float2(lo, hi);
+}
 
 // Row accessors of the on-the-fly quantizer: value i of one input vector.
 // A row of a dense [m][ldx] matrix.
@@ -141,91 +164,146 @@ __global__ __launch_bounds__(256) void k_quantize_stacked(const float *__restric
   quantize_row_wave(x, (int64_t)stack * dim, row, codes, ld, zero, inv_q, sums, lane);
 }
 
-// Partial min/max: set s = rows [s*rps, (s+1)*rps) of a [rows][cols] matrix
-// with leading dimension ldx; part p covers a contiguous slice of the set.
-__global__ __launch_bounds__(256) void k_set_minmax(const float *__restrict__ X, int64_t ldx,
-                                                    int64_t rps, int64_t cols, int nparts,
-                                                    float2 *__restrict__ part) {
-  const int s = blockIdx.y, p = blockIdx.x;
-  const int64_t n = rps * cols;
-  const int64_t per = (n + nparts - 1) / nparts;
-  const int64_t b = (int64_t)p * per, e = b + per < n ? b + per : n;
+// min and max of n contiguous values over the block (every thread); up to
+// eight float4 a thread in flight where the values are 16-byte aligned.
+__device__ __forceinline__ float2 range_minmax_block(const float *__restrict__ x, int64_t n) {
   float lo = INFINITY, hi = -INFINITY;
-  for (int64_t i = b + threadIdx.x; i < e; i += blockDim.x) {
-    const int64_t r = i / cols, c = i - r * cols;
-    const float v = X[(s * rps + r) * ldx + c];
-    lo = fminf(lo, v);
-    hi = fmaxf(hi, v);
-  }
-  lo = wave_min(lo);
-  hi = wave_max(hi);
-  __shared__ float slo[4], shi[4];
-  if ((threadIdx.x & 63) == 0) {
-    slo[threadIdx.x >> 6] = lo;
-    shi[threadIdx.x >> 6] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-      lo = fminf(lo, slo[w]);
-      hi = fmaxf(hi, shi[w]);
+  const int64_t T = blockDim.x;
+  auto take = [&](const float4 &v) {
+    lo = fminf(fminf(lo, v.x), fminf(v.y, fminf(v.z, v.w)));
+    hi = fmaxf(fmaxf(hi, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
+  };
+  int64_t done = 0;
+  if ((((uintptr_t)x) & 15) == 0) {
+    const float4 *x4 = reinterpret_cast<const float4 *>(x);
+    const int64_t n4 = n / 4;
+    int64_t i = threadIdx.x;
+    for (; i + 7 * T < n4; i += 8 * T) {
+      float4 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = x4[i + k * T];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) take(v[k]);
     }
-    part[(int64_t)s * nparts + p] = make_float2(lo, hi);
+    for (; i < n4; i += T) take(x4[i]);
+    done = 4 * n4;
   }
+  for (int64_t i = done + threadIdx.x; i < n; i += T) {
+    lo = fminf(lo, x[i]);
+    hi = fmaxf(hi, x[i]);
+  }
+  return block_minmax(lo, hi);
 }
 
-__global__ void k_set_params(const float2 *__restrict__ part, int nsets, int nparts,
-                             int64_t setsize, double *__restrict__ q_out,
-                             int32_t *__restrict__ z_out, float *__restrict__ iq_out,
-                             double *__restrict__ range, int32_t *__restrict__ zero,
-                             float *__restrict__ inv_q) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nsets) return;
-  float lo = INFINITY, hi = -INFINITY;
-  for (int p = 0; p < nparts; ++p) {
-    lo = fminf(lo, part[(int64_t)s * nparts + p].x);
-    hi = fmaxf(hi, part[(int64_t)s * nparts + p].y);
-  }
-  if (setsize == 0) lo = hi = 0.0f;
-  const QParams p = make_qparams(lo, hi);
-  q_out[s] = p.q;
-  z_out[s] = p.z;
-  iq_out[s] = p.inv_q;
-  if (range) range[s] = p.range;
-  if (zero) zero[s] = p.z;
-  if (inv_q) inv_q[s] = p.inv_q;
+// Quantization of larger sets (a weight matrix, one of its gate blocks, an
+// activation tensor): set s is rows [s * rps, (s + 1) * rps) of a dense
+// [rows][cols] matrix.  Two passes over memory are what it cannot do without
+// (the range is needed before the first code), so it is two launches: partial
+// min/max over up to kSetParts slices of every set, then the encoder, each of
+// whose blocks reduces its set's partials by itself.  16384 x 512 values:
+// 116 us as three launches (min/max of 128 scalar-loading blocks 96, a
+// one-thread reduction of the partials 13, encoder 9), 24 us now.
+__global__ __launch_bounds__(256) void k_set_minmax(const float *__restrict__ X, int64_t setsize,
+                                                    int64_t per, float2 *__restrict__ part) {
+  const int s = blockIdx.y, p = blockIdx.x;
+  const int64_t b = (int64_t)p * per;
+  const int64_t n = b >= setsize ? 0 : (per < setsize - b ? per : setsize - b);
+  const float2 mm = range_minmax_block(X + (int64_t)s * setsize + b, n);
+  if (threadIdx.x == 0) part[(int64_t)s * gridDim.x + p] = mm;
 }
 
-// Encode every row with its set's params; row sums; optional per-row copies of
-// the set's zero point / recovery factor.
-__global__ __launch_bounds__(256) void k_set_encode(
-    const float *__restrict__ X, int64_t ldx, int64_t rows, int64_t cols, int64_t rps,
-    const double *__restrict__ q, const int32_t *__restrict__ zero,
-    const float *__restrict__ inv_q, int8_t *__restrict__ codes, int64_t ld,
-    int32_t *__restrict__ row_sums, int32_t *__restrict__ row_zero,
-    float *__restrict__ row_inv_q) {
+// Where a quantized set goes: codes with row sums, per-set params, optional
+// per-row copies of the set's zero point and recovery factor.
+struct SetOut {
+  int8_t *codes;
+  int64_t ld;
+  double *range;       // per set (nullable, as all below)
+  int32_t *zero;
+  float *inv_q;
+  int32_t *row_sums;   // per row
+  int32_t *row_zero;
+  float *row_inv_q;
+};
+// The block's waves encode rows [r0, r1) of set s.
+__device__ __forceinline__ void encode_set_rows(const float *__restrict__ X, int64_t r0, int64_t r1,
+                                                int64_t cols, const QParams &p, const SetOut &o) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const int64_t s = row / rps;
-  const int sum =
-      encode_row_wave(DenseRow{X + row * ldx}, cols, codes + row * ld, ld, q[s], zero[s], lane);
-  if (lane == 0) {
-    if (row_sums) row_sums[row] = sum;
-    if (row_zero) row_zero[row] = zero[s];
-    if (row_inv_q) row_inv_q[row] = inv_q[s];
+  for (int64_t row = r0 + (threadIdx.x >> 6); row < r1; row += blockDim.x >> 6) {
+    const int sum =
+        encode_row_wave(DenseRow{X + row * cols}, cols, o.codes + row * o.ld, o.ld, p.q, p.z, lane);
+    if (lane == 0) {
+      if (o.row_sums) o.row_sums[row] = sum;
+      if (o.row_zero) o.row_zero[row] = p.z;
+      if (o.row_inv_q) o.row_inv_q[row] = p.inv_q;
+    }
   }
 }
+__device__ __forceinline__ void put_set_params(const QParams &p, int64_t s, const SetOut &o) {
+  if (o.range) o.range[s] = p.range;
+  if (o.zero) o.zero[s] = p.z;
+  if (o.inv_q) o.inv_q[s] = p.inv_q;
+}
 
-__global__ void k_dequantize(const int8_t *__restrict__ codes, int64_t ld, int64_t rows,
-                             int64_t cols, int64_t rpb, const int32_t *__restrict__ zero,
-                             const float *__restrict__ inv_q, float *__restrict__ dst) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * cols) return;
-  const int64_t r = i / cols, c = i - r * cols;
+__global__ __launch_bounds__(256) void k_set_encode(const float *__restrict__ X, int64_t rps,
+                                                    int64_t cols,
+                                                    const float2 *__restrict__ part, int nparts,
+                                                    SetOut o) {
+  const int64_t s = blockIdx.y;
+  float lo = INFINITY, hi = -INFINITY;
+  for (int i = threadIdx.x; i < nparts; i += 256) {
+    const float2 v = part[s * nparts + i];
+    lo = fminf(lo, v.x);
+    hi = fmaxf(hi, v.y);
+  }
+  const float2 mm = block_minmax(lo, hi);
+  const QParams p = make_qparams(mm.x, mm.y);
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_set_params(p, s, o);
+  const int64_t r0 = (int64_t)blockIdx.x * kEncodeRows;
+  encode_set_rows(X, s * rps + r0, s * rps + (r0 + kEncodeRows < rps ? r0 + kEncodeRows : rps), cols,
+                  p, o);
+}
+
+// Small sets, one block each: range, params and codes in one launch (the
+// second read hits the CU's cache).
+__global__ __launch_bounds__(1024) void k_set_small(const float *__restrict__ X, int64_t rps,
+                                                    int64_t cols, SetOut o) {
+  const int64_t s = blockIdx.x;
+  float2 mm = range_minmax_block(X + s * rps * cols, rps * cols);
+  if (cols == 0) mm = make_float2(0.0f, 0.0f);
+  const QParams p = make_qparams(mm.x, mm.y);
+  if (threadIdx.x == 0) put_set_params(p, s, o);
+  encode_set_rows(X, s * rps, (s + 1) * rps, cols, p, o);
+}
+
+// Recovery (eq. 3), one wave per row: four codes per lane and load where the
+// rows of both sides are aligned for it.
+__global__ __launch_bounds__(256) void k_dequantize(const int8_t *__restrict__ codes, int64_t ld,
+                                                    int64_t rows, int64_t cols, int64_t rpb,
+                                                    const int32_t *__restrict__ zero,
+                                                    const float *__restrict__ inv_q,
+                                                    float *__restrict__ dst, int vec) {
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
+  if (r >= rows) return;
   const int64_t b = r / rpb;
-  const int v = (int)codes[r * ld + c] + 128;  // V'
-  dst[i] = (float)(v + zero[b]) * inv_q[b];
+  const int z = zero[b] + 128;  // V' = code + 128
+  const float iq = inv_q[b];
+  const int8_t *c = codes + r * ld;
+  float *d = dst + r * cols;
+  int64_t done = 0;
+  if (vec) {
+    for (int64_t i = lane; i < cols / 4; i += kWave) {
+      const uint32_t w = reinterpret_cast<const uint32_t *>(c)[i];
+      float4 v;
+      v.x = (float)((int)(int8_t)w + z) * iq;
+      v.y = (float)((int)(int8_t)(w >> 8) + z) * iq;
+      v.z = (float)((int)(int8_t)(w >> 16) + z) * iq;
+      v.w = (float)((int)(int8_t)(w >> 24) + z) * iq;
+      reinterpret_cast<float4 *>(d)[i] = v;
+    }
+    done = cols / 4 * 4;
+  }
+  for (int64_t i = done + lane; i < cols; i += kWave) d[i] = (float)((int)c[i] + z) * iq;
 }
 
 // Row sums of 0..255 codes stored in the signed layout.
@@ -271,31 +349,42 @@ hipError_t launch_quantize_stacked(const float *frames, int64_t B, int dim, int 
   return hipGetLastError();
 }
 
-size_t set_quantize_ws(int nsets) {
-  return align_up((size_t)nsets * kSetParts * sizeof(float2), 256) +
-         3 * align_up((size_t)nsets * sizeof(double), 256);
+// Slices of a set's partial min/max: 8192 values a block (eight float4 per
+// thread, one round of loads) up to 512 blocks, beyond which a block's further
+// rounds cost less than longer reductions of the partials.
+static int set_parts(int64_t setsize) {
+  return (int)std::min<int64_t>(kSetParts, std::max<int64_t>(1, (setsize + 8191) / 8192));
+}
+// Sets that one block takes whole: up to 8192 values, one round of its loads.
+// Beyond (more where there are many sets to fill the chip with blocks), two
+// launches over all CUs beat one block's passes.
+static bool set_is_small(int64_t setsize, int64_t nsets) {
+  return setsize <= 8192 || (setsize <= 65536 && nsets >= 256);
 }
 
-hipError_t launch_set_quantize(const float *X, int64_t ldx, int64_t rows, int64_t cols,
-                               int nsets, int8_t *codes, int64_t ld, double *range,
-                               int32_t *zero, float *inv_q, int32_t *row_sums,
-                               int32_t *row_zero, float *row_inv_q, void *ws, hipStream_t s) {
+size_t set_quantize_ws(int64_t rows, int64_t cols, int nsets) {
+  const int64_t n = nsets > 0 ? rows / nsets * cols : 0;
+  return align_up((size_t)nsets * set_parts(n) * sizeof(float2), 256);
+}
+
+hipError_t launch_set_quantize(const float *X, int64_t rows, int64_t cols, int nsets, int8_t *codes,
+                               int64_t ld, double *range, int32_t *zero, float *inv_q,
+                               int32_t *row_sums, int32_t *row_zero, float *row_inv_q, void *ws,
+                               hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  char *w = static_cast<char *>(ws);
-  float2 *part = reinterpret_cast<float2 *>(w);
-  w += align_up((size_t)nsets * kSetParts * sizeof(float2), 256);
-  double *q = reinterpret_cast<double *>(w);
-  w += align_up((size_t)nsets * sizeof(double), 256);
-  int32_t *zs = reinterpret_cast<int32_t *>(w);
-  w += align_up((size_t)nsets * sizeof(double), 256);
-  float *iqs = reinterpret_cast<float *>(w);
-  const int64_t rps = rows / nsets;
-  hipLaunchKernelGGL(k_set_minmax, dim3(kSetParts, nsets), dim3(256), 0, s, X, ldx, rps, cols,
-                     kSetParts, part);
-  hipLaunchKernelGGL(k_set_params, dim3(blocks_for(nsets, 64)), dim3(64), 0, s, part, nsets,
-                     kSetParts, rps * cols, q, zs, iqs, range, zero, inv_q);
-  hipLaunchKernelGGL(k_set_encode, dim3(blocks_for(rows, 4)), dim3(256), 0, s, X, ldx, rows,
-                     cols, rps, q, zs, iqs, codes, ld, row_sums, row_zero, row_inv_q);
+  const SetOut o{codes, ld, range, zero, inv_q, row_sums, row_zero, row_inv_q};
+  const int64_t rps = rows / nsets, n = rps * cols;
+  if (set_is_small(n, nsets)) {
+    hipLaunchKernelGGL(k_set_small, dim3(nsets), dim3(n <= 4096 && nsets > 1 ? 256 : 1024), 0, s, X,
+                       rps, cols, o);
+    return hipGetLastError();
+  }
+  float2 *part = static_cast<float2 *>(ws);
+  const int parts = set_parts(n);
+  const int64_t per = round_up((n + parts - 1) / parts, 4);
+  hipLaunchKernelGGL(k_set_minmax, dim3(parts, nsets), dim3(256), 0, s, X, n, per, part);
+  hipLaunchKernelGGL(k_set_encode, dim3(blocks_for(rps, kEncodeRows), nsets), dim3(256), 0, s, X,
+                     rps, cols, part, parts, o);
   return hipGetLastError();
 }
 
@@ -303,8 +392,11 @@ hipError_t launch_dequantize(const int8_t *codes, int64_t ld, int64_t rows, int6
                              int nblocks, const int32_t *zero, const float *inv_q, float *dst,
                              hipStream_t s) {
   if (rows * cols == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_dequantize, dim3(blocks_for(rows * cols, 256)), dim3(256), 0, s, codes,
-                     ld, rows, cols, rows / nblocks, zero, inv_q, dst);
+  // every row of codes 4-byte aligned, every row of dst 16-byte aligned
+  const int vec = ld % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0 && cols % 4 == 0 &&
+                  reinterpret_cast<uintptr_t>(dst) % 16 == 0;
+  hipLaunchKernelGGL(k_dequantize, dim3(blocks_for(rows, 4)), dim3(256), 0, s, codes, ld, rows, cols,
+                     rows / nblocks, zero, inv_q, dst, vec);
   return hipGetLastError();
 }
 

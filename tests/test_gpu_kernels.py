@@ -211,3 +211,13 @@ def test_quantize_activations_per_vector(ql, orc, m, cols):
     assert np.array_equal(q.inv_q.cpu().numpy().view(np.uint32), o.inv_q.view(np.uint32))
     assert np.array_equal(q.sums.cpu().numpy(), o.codes.astype(np.int64).sum(1))
     assert (q.codes[:, cols:] == 0).all()
+
+
+# Edges of the set quantizer's launches: one block per set up to 8192 values,
+# two launches beyond, up to 65536 a block with 256 sets or more; sets that
+# start off a 16-byte boundary; more than 512 slices of 8192 values.
+@pytest.mark.parametrize("rows,cols,nblocks", [(64, 128, 1), (1, 8193, 1), (3, 8191, 3), (9, 2731, 3),
+                                               (512, 65, 512), (512, 257, 256), (30, 4097, 2),
+                                               (8300, 511, 1), (40, 1030, 1)])
+def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
+    test_quantize_matches_oracle(ql, orc, rows, cols, nblocks)
