@@ -660,100 +660,189 @@ __global__ __launch_bounds__(64 * WM *WN) void k_gemm(const int8_t *__restrict__
     }
   }
 
-  if (EPI == EPI_RECOVER || EPI == EPI_RAW || EPI == EPI_SMAX_OUT) {
 #pragma unroll
-    for (int i = 0; i < C::FM; ++i)
+  for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lr = wm * C::TM + i * 32 + frag_row(r, lane);
-        const int64_t m = m0 + lr;
-        if (m >= M) continue;
-        const int32_t sigx = e.x_sums[m] - 128 * (int32_t)K;
-        int32_t ztx = 0;
-        float iqx = 0.0f;
-        if (EPI != EPI_RAW) {
-          ztx = e.x_zero[m] + 128;
-          iqx = e.x_inv_q[m];
-        }
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-          const int64_t n = ncol[j];
-          if (n >= N) continue;
-          const int32_t S = acc[i][j][r];
-          if (EPI == EPI_RAW) {
-            e.acc[m * N + n] = acc_u8(S, sigw[j], sigx, K);
-          } else {
-            const float y = recover(S, colterm[j], ztw[j], ztx, sigx, iqw[j], iqx) + bn[j];
-            if (EPI == EPI_RECOVER) {
-              e.Y[m * N + n] = y;
-              if (e.acc) e.acc[m * N + n] = acc_u8(S, sigw[j], sigx, K);
-            } else {
-              e.Y[m * N + n] = __expf(y - rowmax[lr]) * rowinv[lr];
-            }
-          }
-        }
-      }
-  } else {  // EPI_SMAX_STATS: per-row (max, sum exp) over this tile's columns
-    float *red = reinterpret_cast<float *>(smem);  // [WN][BM] scratch (stages are free now)
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lr = wm * C::TM + i * 32 + frag_row(r, lane);
-        const int64_t m = m0 + lr;
-        const int64_t mm = m < M ? m : M - 1;
-        const int32_t sigx = e.x_sums[mm] - 128 * (int32_t)K;
-        const int32_t ztx = e.x_zero[mm] + 128;
-        const float iqx = e.x_inv_q[mm];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-          const int64_t n = ncol[j];
-          const float y = recover(acc[i][j][r], colterm[j], ztw[j], ztx, sigx, iqw[j], iqx) + bn[j];
-          if (n < N) {
-            mx = fmaxf(mx, y);
-            if (m < M) {
-              if (e.logits) e.logits[m * N + n] = y;
-              if (e.acc) e.acc[m * N + n] = acc_u8(acc[i][j][r], sigw[j], sigx, K);
-            }
-          }
-          // stash y in the accumulator register as float bits for the sum pass
-          acc[i][j][r] = __float_as_int(y);
-        }
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        if ((lane & 31) == 0) red[wn * BM + lr] = mx;
-      }
-    __syncthreads();
-    float *tmax = red + WN * BM;  // [BM]
-    for (int r = threadIdx.x; r < BM; r += C::NT) {
-      float mx = -INFINITY;
-      for (int w = 0; w < WN; ++w) mx = fmaxf(mx, red[w * BM + r]);
-      tmax[r] = mx;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lr = wm * C::TM + i * 32 + frag_row(r, lane);
-        const float mx = tmax[lr];
-        float sm = 0.0f;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j)
-          if (ncol[j] < N) sm += __expf(__int_as_float(acc[i][j][r]) - mx);
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) sm += __shfl_xor(sm, o, 64);
-        if ((lane & 31) == 0) red[wn * BM + lr] = sm;
-      }
-    __syncthreads();
-    for (int r = threadIdx.x; r < BM; r += C::NT) {
-      const int64_t m = m0 + r;
+    for (int r = 0; r < 16; ++r) {
+      const int lr = wm * C::TM + i * 32 + frag_row(r, lane);
+      const int64_t m = m0 + lr;
       if (m >= M) continue;
-      float sm = 0.0f;
-      for (int w = 0; w < WN; ++w) sm += red[w * BM + r];
-      e.stats[m * e.ntn + tn] = make_float2(tmax[r], sm);
+      const int32_t sigx = e.x_sums[m] - 128 * (int32_t)K;
+      int32_t ztx = 0;
+      float iqx = 0.0f;
+      if (EPI != EPI_RAW) {
+        ztx = e.x_zero[m] + 128;
+        iqx = e.x_inv_q[m];
+      }
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j) {
+        const int64_t n = ncol[j];
+        if (n >= N) continue;
+        const int32_t S = acc[i][j][r];
+        if (EPI == EPI_RAW) {
+          e.acc[m * N + n] = acc_u8(S, sigw[j], sigx, K);
+        } else {
+          e.Y[m * N + n] = recover(S, colterm[j], ztw[j], ztx, sigx, iqw[j], iqx) + bn[j];
+          if (e.acc) e.acc[m * N + n] = acc_u8(S, sigw[j], sigx, K);
+        }
+      }
     }
+}
+
+// Products of few rows (or few tiles): W' is what has to be read, so every
+// wave takes 16 of its rows, whole, straight into registers as MFMA fragments
+// (no LDS, no barrier), against MB 16-row blocks of X, whose codes the waves
+// of a CU share through its cache.  Waves, not tiles, fill the chip: N = 8192
+// is 512 of them per 16 MB rows, where 128 x 128 tiles are 64 workgroups that
+// each wait four times for a 32 KB stage.  The 16 x 16 result leaves a lane
+// four neighbouring columns of one row: one 16-byte store.
+constexpr int kSkinnyWaves = 2;
+template <int MB>
+__global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_skinny(
+    const int8_t *__restrict__ A, int64_t lda, const int8_t *__restrict__ B, int64_t ldb, int64_t M,
+    int64_t N, int64_t K, EpiArgs e) {
+  const int lane = threadIdx.x & 63, fr = lane & 15, fq = lane >> 4;
+  const int64_t n0 = ((int64_t)blockIdx.x * kSkinnyWaves + (threadIdx.x >> 6)) * 16;
+  const int64_t m0 = (int64_t)blockIdx.y * 16 * MB;
+  if (n0 >= N) return;
+  const int64_t wrow = n0 + fr < N ? n0 + fr : N - 1;
+  const int8_t *w = B + wrow * ldb + 16 * fq;
+  const int8_t *x[MB];
+#pragma unroll
+  for (int b = 0; b < MB; ++b) {
+    const int64_t m = m0 + 16 * b + fr;
+    x[b] = A + (m < M ? m : M - 1) * lda + 16 * fq;
+  }
+  v4i acc[MB];
+#pragma unroll
+  for (int b = 0; b < MB; ++b) acc[b] = v4i{};
+  const int nk = (int)((K + 63) / 64);  // both leading dimensions cover 64 nk
+  int c = 0;
+  for (; c + 8 <= nk; c += 8) {
+    v4i wf[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) wf[k] = *reinterpret_cast<const v4i *>(w + (c + k) * 64);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int b = 0; b < MB; ++b)
+        acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+            wf[k], *reinterpret_cast<const v4i *>(x[b] + (c + k) * 64), acc[b], 0, 0, 0);
+  }
+  for (; c < nk; ++c) {
+    const v4i wf = *reinterpret_cast<const v4i *>(w + c * 64);
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+      acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+          wf, *reinterpret_cast<const v4i *>(x[b] + c * 64), acc[b], 0, 0, 0);
+  }
+  // lane: columns n0 + 4 fq .. + 3 of row m0 + 16 b + fr
+  const int64_t nc = n0 + 4 * fq;
+  if (nc >= N) return;
+  int32_t ztw[4], sigw[4];
+  int64_t colterm[4];
+  float iqw[4], bn[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int64_t nn = nc + t < N ? nc + t : N - 1;
+    const int64_t blk = nn / e.w_rpb;
+    ztw[t] = e.w_zero[blk] + 128;
+    sigw[t] = e.w_sums[nn] - 128 * (int32_t)K;
+    colterm[t] = (int64_t)sigw[t] + K * (int64_t)ztw[t];
+    iqw[t] = e.w_inv_q[blk];
+    bn[t] = e.bias ? e.bias[nn] : 0.0f;
+  }
+  const bool vec = (N & 3) == 0;  // rows of Y and acc 16-byte aligned
+#pragma unroll
+  for (int b = 0; b < MB; ++b) {
+    const int64_t m = m0 + 16 * b + fr;
+    if (m >= M) continue;
+    const int32_t sigx = e.x_sums[m] - 128 * (int32_t)K, ztx = e.x_zero[m] + 128;
+    const float iqx = e.x_inv_q[m];
+    float y[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      y[t] = recover(acc[b][t], colterm[t], ztw[t], ztx, sigx, iqw[t], iqx) + bn[t];
+    const int64_t off = m * N + nc;
+    if (vec && ((uintptr_t)e.Y & 15) == 0) {
+      *reinterpret_cast<float4 *>(e.Y + off) = make_float4(y[0], y[1], y[2], y[3]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (nc + t < N) e.Y[off + t] = y[t];
+    }
+    if (e.acc)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (nc + t < N) e.acc[off + t] = acc_u8(acc[b][t], sigw[t], sigx, K);
+  }
+}
+
+// Softmax of logit rows already in `post`, in place: one workgroup per row.
+// Per 128 columns (max, sum exp) by one half-wave, lane c holding columns c,
+// c + 32, c + 64 and c + 96; the sums of the two 64-column halves by a
+// butterfly each, added; then the tiles' sums, rescaled to the row's max, in
+// tile order.  The order is fixed, whatever the number of rows.
+constexpr int kSmaxThreads = 1024;
+__global__ __launch_bounds__(kSmaxThreads) void k_smax_rows(float *__restrict__ post, int64_t N,
+                                                            int ntn, float2 *__restrict__ stats,
+                                                            float *__restrict__ logits) {
+  constexpr int HW = kSmaxThreads / 32;
+  __shared__ float smax[kSmaxThreads / 64], sp[1024];
+  const int64_t m = blockIdx.x;
+  float *y = post + m * N;
+  float2 *st = stats + m * ntn;
+  const int tid = threadIdx.x, c = tid & 31, hw = tid >> 5;
+  float rmx = -INFINITY;
+  for (int t = hw; t < ntn; t += HW) {
+    const int64_t n0 = (int64_t)t * 128 + c;
+    float v[4], mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = n0 + 32 * j < N ? y[n0 + 32 * j] : -INFINITY;
+      mx = fmaxf(mx, v[j]);
+      if (logits && n0 + 32 * j < N) logits[m * N + n0 + 32 * j] = v[j];
+    }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float s[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      s[h] = 0.0f;
+#pragma unroll
+      for (int j = 2 * h; j < 2 * h + 2; ++j)
+        if (n0 + 32 * j < N) s[h] += __expf(v[j] - mx);
+    }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) s[h] += __shfl_xor(s[h], o, 64);
+    if (c == 0) st[t] = make_float2(mx, s[0] + s[1]);
+    rmx = fmaxf(rmx, mx);
+  }
+  rmx = fmaxf(rmx, __shfl_xor(rmx, 32, 64));
+  if ((tid & 63) == 0) smax[tid >> 6] = rmx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSmaxThreads / 64; ++w) rmx = fmaxf(rmx, smax[w]);
+  float sm = 0.0f;
+  for (int t0 = 0; t0 < ntn; t0 += 1024) {
+    if (t0 + tid < ntn) {
+      const float2 p = st[t0 + tid];
+      sp[tid] = p.y * __expf(p.x - rmx);
+    }
+    __syncthreads();
+    const int n = ntn - t0 < 1024 ? ntn - t0 : 1024;
+#pragma unroll 8
+    for (int k = 0; k < n; ++k) sm += sp[k];
+    __syncthreads();
+  }
+  const float inv = 1.0f / sm;
+  for (int t = hw; t < ntn; t += HW) {
+    const int64_t n0 = (int64_t)t * 128 + c;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (n0 + 32 * j < N) y[n0 + 32 * j] = __expf(y[n0 + 32 * j] - rmx) * inv;
   }
 }
 
@@ -765,10 +854,6 @@ static hipError_t run(const int8_t *A, int64_t lda, const int8_t *B, int64_t ldb
   const int64_t Kp = round_up(K, BK);
   size_t lds = (size_t)C::LDS;
   if (EPI == EPI_SMAX_OUT) lds += 2 * BM * sizeof(float);
-  if (EPI == EPI_SMAX_STATS) {
-    const size_t need = (size_t)(WN + 1) * BM * sizeof(float);
-    lds = lds > need ? lds : need;
-  }
   auto kern = k_gemm<BM, BN, BK, WM, WN, NS, EPI>;
   static bool attr_set = false;  // per instantiation; idempotent
   if (!attr_set) {
@@ -784,10 +869,20 @@ static hipError_t run(const int8_t *A, int64_t lda, const int8_t *B, int64_t ldb
 
 // Kp must stay within the padded leading dimensions: with ld a multiple of 64
 // and BK = 64 this always holds; BK = 128 is used when both ld allow it.
-// Column width of the tiles a product of M x N uses: 256 once there are
-// enough 256x256 tiles to fill the chip, else 128.
-static int big_tile_n(int64_t M, int64_t N) {
-  return ((M + 255) / 256) * ((N + 255) / 256) >= 256 ? 256 : 128;
+// Whether a product of M x N takes 256x256 tiles: once there are enough of
+// them to fill the chip.
+static bool big_tiles(int64_t M, int64_t N) {
+  return ((M + 255) / 256) * ((N + 255) / 256) >= 256;
+}
+
+static hipError_t run_skinny(const int8_t *A, int64_t lda, const int8_t *B, int64_t ldb, int64_t M,
+                             int64_t N, int64_t K, const EpiArgs &e, hipStream_t s) {
+  const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  auto kern = mb == 1 ? k_gemm_skinny<1> : mb == 2 ? k_gemm_skinny<2> : k_gemm_skinny<4>;
+  const dim3 grid((unsigned)((N + 16 * kSkinnyWaves - 1) / (16 * kSkinnyWaves)),
+                  (unsigned)((M + 16 * mb - 1) / (16 * mb)));
+  hipLaunchKernelGGL(kern, grid, dim3(64 * kSkinnyWaves), 0, s, A, lda, B, ldb, M, N, K, e);
+  return hipGetLastError();
 }
 
 template <int EPI>
@@ -797,7 +892,7 @@ static hipError_t dispatch(const int8_t *A, int64_t lda, const int8_t *B, int64_
   const bool k128 = round_up(K, 128) <= lda && round_up(K, 128) <= ldb;
   // 256x256 tiles (128x128 per wave) once there are enough of them to fill
   // the chip; otherwise 128x128 tiles (64x64 per wave)
-  if (big_tile_n(M, N) == 256) {
+  if (big_tiles(M, N)) {
     if constexpr (EPI != EPI_RAW) {
       // recovering epilogues: 8 waves of 128x64 (two per SIMD, so one wave's
       // epilogue stalls hide behind the other's work)
@@ -807,8 +902,22 @@ static hipError_t dispatch(const int8_t *A, int64_t lda, const int8_t *B, int64_
     if (k128) return run<256, 256, 128, 2, 2, 2, EPI>(A, lda, B, ldb, M, N, K, e, s);
     return run<256, 256, 64, 2, 2, 4, EPI>(A, lda, B, ldb, M, N, K, e, s);
   }
-  if (k128) return run<128, 128, 128, 2, 2, 0, EPI>(A, lda, B, ldb, M, N, K, e, s);
-  return run<128, 128, 64, 2, 2, 0, EPI>(A, lda, B, ldb, M, N, K, e, s);
+  if constexpr (EPI == EPI_RECOVER) {
+    // 128x128 tiles for less than every CU leave the chip idle; but the few-row
+    // kernel reads X through the caches once per 16 columns, so its time grows
+    // with tiles x K and meets the tiles' at about 80 000.  Per-row product,
+    // quantization included, us, tiles then few-row: 64 x 8192 x 512 (64
+    // tiles) 23.9 and 18.7; 4000 x 500 x 512 (128) 27.4 and 25.9; 8000 x 500 x
+    // 320 (252) 30.0 and 29.4; 8000 x 500 x 512 (252) 31.8 and 40.6; 256 x
+    // 8192 x 1024 (128) 29.0 and 32.2.
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    if (tiles < 256 && tiles * K < 80000) return run_skinny(A, lda, B, ldb, M, N, K, e, s);
+  }
+  if constexpr (EPI == EPI_RECOVER || EPI == EPI_RAW) {
+    if (k128) return run<128, 128, 128, 2, 2, 0, EPI>(A, lda, B, ldb, M, N, K, e, s);
+    return run<128, 128, 64, 2, 2, 0, EPI>(A, lda, B, ldb, M, N, K, e, s);
+  }
+  return hipErrorInvalidValue;  // the softmax passes run on big tiles only
 }
 
 static EpiArgs make_epi(const ActRows &X, const WeightMat &W, const float *bias) {
@@ -874,8 +983,22 @@ hipError_t launch_softmax_layer(const ActRows &X, const WeightMat &W, int64_t M,
                                 float *logits, void *ws, hipStream_t s) {
   EpiArgs e = make_epi(X, W, bias);
   e.stats = static_cast<float2 *>(ws);
-  const int tn = big_tile_n(M, N);
-  e.ntn = (int)((N + tn - 1) / tn);
+  if (!big_tiles(M, N)) {
+    // fewer tiles: the product once, into post, and the rows normalised there
+    // (a whole forward with 8192 states, us, as the two passes below on 128x128
+    // tiles with a combining launch between them, and now: 1 row 95 and 57, 64
+    // rows 123 and 66, 500 rows 134 and 88, 1900 rows 138 and 127)
+    e.Y = post;
+    e.acc = acc;
+    const hipError_t err = dispatch<EPI_RECOVER>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);
+    if (err != hipSuccess || M == 0 || N == 0) return err;
+    hipLaunchKernelGGL(k_smax_rows, dim3((unsigned)M), dim3(kSmaxThreads), 0, s, post, N,
+                       (int)((N + 127) / 128), e.stats, logits);
+    return hipGetLastError();
+  }
+  // many rows: post is written once; two passes of the product instead of
+  // three over M x N floats
+  e.ntn = (int)((N + 255) / 256);
   e.acc = acc;
   e.logits = logits;
   hipError_t err = dispatch<EPI_SMAX_STATS>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);

@@ -221,3 +221,31 @@ def test_quantize_activations_per_vector(ql, orc, m, cols):
                                                (8300, 511, 1), (40, 1030, 1)])
 def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
     test_quantize_matches_oracle(ql, orc, rows, cols, nblocks)
+
+
+# Products of few tiles: one, two and four 16-row blocks a wave, rows and
+# columns one off its 16, K around its 64-byte steps and its unrolled 512.
+@pytest.mark.parametrize("m,rows,cols", [(1, 15, 63), (16, 17, 64), (17, 33, 65), (32, 100, 511),
+                                         (33, 31, 512), (64, 16, 513), (65, 130, 577), (200, 4, 1100)])
+@pytest.mark.parametrize("gran", [0, 1])
+def test_qmatmul_few_rows(ql, orc, m, rows, cols, gran):
+    test_qmatmul_ragged_shapes(ql, orc, m, rows, cols, 1, gran)
+
+
+# Row softmax in place: states below, at and above a 128-column tile, more
+# tiles than half-waves, more than one 1024-tile round; rows on either side of
+# the 16-row blocks.
+@pytest.mark.parametrize("m,S", [(1, 1), (3, 127), (16, 128), (17, 129), (5, 4100), (2, 131100)])
+def test_softmax_few_rows(ql, orc, m, S):
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(8, 8, 1, states=S, seed=S)
+    x = np.random.default_rng(m).standard_normal((m, 1, 8)).astype(np.float32)
+    g = ql.acoustic_model_forward(ql.quantize_model(w), torch.from_numpy(x).cuda(), taps=True)
+    o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
+    assert np.array_equal(g["logits"].cpu().numpy(), o["logits"])
+    post = g["post"].cpu().numpy().astype(np.float64)
+    # exp of a float difference of logits |y| < 8 and a sum of at most 2^17 terms
+    assert np.max(np.abs(post - o["post"])) <= 1e-4
+    assert np.max(np.abs(post.sum(-1) - 1.0)) < 1e-5
+    plain = ql.acoustic_model_forward(ql.quantize_model(w), torch.from_numpy(x).cuda())["post"]
+    assert torch.equal(plain, g["post"])
