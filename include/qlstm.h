@@ -403,7 +403,9 @@ const char *ql_status_str(ql_status s);
  * workgroup wait of their persistent kernels to `polls` re-reads (0 restores
  * the default bound), so a wait that is not met within them expires, every
  * workgroup leaves at its next wait, and ql_workspace_status reports
- * QL_ETIMEOUT (the outputs are then undefined).  Applies to every device of
+ * QL_ETIMEOUT (the outputs are then undefined).  While a bound is set, one
+ * workgroup of each group that keeps in step by itself starts some 30 us late,
+ * so that a wait is there to expire.  Applies to every device of
  * the process (none: nothing to do) and must not overlap a call of this
  * library in flight; QL_EINVAL for a negative count, QL_EHIP if a device
  * could not be set. */

@@ -567,6 +567,9 @@ hipError_t launch_recurrent_f32(const F32RecArgs &a, hipStream_t s, bool *unsupp
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
+  bool done = false;
+  e = launch_xrec_f32(a, cus, lds_max, s, &done);
+  if (e != hipSuccess || done) return e;
   F32Tiling tl;
   if (!plan_f32(a, cus, lds_max, &tl)) {
     *unsupported = true;

@@ -113,6 +113,7 @@ hipError_t set_wait_bound_f32(int polls);
 hipError_t set_wait_bound_train(int polls);
 hipError_t set_wait_bound_xrec(int polls);
 hipError_t set_wait_bound_xstack(int polls);
+hipError_t set_wait_bound_xf32(int polls);
 // Reads the timeout flag a persistent launch left in its workspace (syncs s).
 hipError_t recurrent_timed_out(const void *ws, hipStream_t s, bool *timed_out);
 // Zeroes the n64 64-bit words after the workspace header (counters first).
@@ -229,6 +230,10 @@ struct F32RecArgs {
 };
 size_t recurrent_f32_ws(int64_t B, int64_t H, int64_t P);
 hipError_t launch_recurrent_f32(const F32RecArgs &a, hipStream_t s, bool *unsupported);
+// Layers without a projection on the whole chip (ql_xf32.hip): each XCD runs
+// an eighth of the batch.  *done false when the shapes or the device do not
+// fit that layout (nothing launched).
+hipError_t launch_xrec_f32(const F32RecArgs &a, int cus, int lds_max, hipStream_t s, bool *done);
 
 // ---- quantization-aware training step (ql_train.hip)
 // Cross-entropy of the posteriors post [N][S] against targets [N]: dC/dz =

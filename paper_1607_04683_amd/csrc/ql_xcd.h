@@ -36,6 +36,14 @@ __device__ __forceinline__ void wait_vmcnt0() {
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
 }
 
+// While the test hook bounds the waits, the calling workgroup starts some 30 us
+// late, so that the others' first wait is not met at once: workgroups that
+// keep in step by themselves may never need a re-read.
+__device__ __forceinline__ void straggle_under_wait_bound() {
+  if (g_wait_it0 != 0)
+    for (int i = 0; i < 8; ++i) __builtin_amdgcn_s_sleep(127);
+}
+
 // Re-reads the words addr(i), i < N, whose bit is set in `need` until each
 // carries `tag`; the payloads go to v.  A word is read again only while its
 // tag has not matched.  False if the wait expired.

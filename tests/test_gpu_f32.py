@@ -110,3 +110,18 @@ def test_f32_model_B64_sampled_utterance(ql, orc):
     g = ql.f32_acoustic_model_forward(ql.f32_model(w), dev(x))["post"][:, 45].cpu().numpy()
     o = orc.acoustic_model_forward_f32(w, x[:, 45:46])["post"][:, 0]
     assert np.max(np.abs(g - o)) <= TOL
+
+
+@pytest.mark.parametrize("H,T,B", [
+    (1, 3, 1),       # one cell, one row
+    (15, 2, 8),      # a tile one cell short; one row on every XCD
+    (17, 4, 9),      # a second tile of one cell; 2 rows, the last XCDs without
+    (512, 2, 33),    # every tile full; 5 rows: a second row group of one
+    (500, 3, 64),    # 8 rows per XCD
+    (96, 1, 65),     # 9 rows: the 16-row form; one frame
+    (260, 3, 128),   # a full launch
+    (36, 3, 129),    # one row more than a launch holds
+])
+def test_f32_layer_xcd_rows(ql, orc, H, T, B):
+    """The layout with an eighth of the batch per XCD at its edges."""
+    _layer(ql, orc, 24, H, 0, T, B, seed=H + T + B, h0c0=B % 2 == 1)
