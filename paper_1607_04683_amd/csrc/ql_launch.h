@@ -114,6 +114,7 @@ hipError_t set_wait_bound_train(int polls);
 hipError_t set_wait_bound_xrec(int polls);
 hipError_t set_wait_bound_xstack(int polls);
 hipError_t set_wait_bound_xf32(int polls);
+hipError_t set_wait_bound_xbptt(int polls);
 // Reads the timeout flag a persistent launch left in its workspace (syncs s).
 hipError_t recurrent_timed_out(const void *ws, hipStream_t s, bool *timed_out);
 // Zeroes the n64 64-bit words after the workspace header (counters first).
@@ -258,5 +259,10 @@ struct BpttArgs {
 };
 size_t bptt_ws(int64_t T, int64_t B);
 hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported);
+// The same on the whole chip (ql_xbptt.hip): each XCD runs an eighth of the
+// batch.  *done false when the shapes or the device do not fit that layout
+// (nothing launched).
+size_t xbptt_ws(int64_t B);
+hipError_t launch_xbptt(const BpttArgs &a, int cus, int lds_max, hipStream_t s, bool *done);
 
 }  // namespace ql

@@ -141,12 +141,8 @@ hipError_t launch_sgd(float *w, const float *g, int64_t n, float lr, hipStream_t
 // added in wave order (the result does not depend on timing); then the
 // cell's backward step and its part of da_t.  Counters are per step, so
 // nothing is reused in a launch.
-// On the whole chip (8 XCDs of 32 CUs) with at most 8 batch slices of at most
-// 32 tiles, every CU gets a workgroup, which reads its XCC_ID and takes the
-// next free slot of its XCD: tile `slot` of slice `XCC_ID`.  A slice's tiles
-// then share one L2 for the da_{t+1} they all read.  da_t still goes out with
-// device-coherent stores: the gradient products launched after this kernel
-// read it from every XCD.
+// This is the layout of a partition of the chip; the whole chip runs the
+// recurrence with an eighth of the batch per XCD (ql_xbptt.hip).
 // ---------------------------------------------------------------------------
 constexpr int kBpttThreads = 512;
 constexpr int kBpttWaves = kBpttThreads / 64;
@@ -154,11 +150,8 @@ constexpr int kBpttKBlocks = 4;  // 64-k blocks per wave: 8 x 4 x 64 = 2048 >= 4
 
 constexpr int kBpttLdw = kBpttWaves * kBpttKBlocks * 64 + 4;  // padded row of W_h^T (floats)
 
-constexpr int kBpttXcds = 8, kBpttXcdCus = 32;
-constexpr int kBpttSlotBytes = kBpttXcds * 64;  // per-XCD slot counters after the header
-
 struct BpttTiling {
-  int bB, u, nbt, nut, grid, xcd;
+  int bB, u, nbt, nut, grid;
   size_t off_w, off_p, off_dc, lds_bytes;
 };
 
@@ -173,27 +166,10 @@ __global__ __launch_bounds__(kBpttThreads) void k_bptt(BpttArgs a, BpttTiling tl
   const int tid = threadIdx.x;
   const int64_t T = a.T, B = a.B, H = a.H, G4 = 4 * a.H;
   int *flag = reinterpret_cast<int *>(a.ws) + kHdrFlag;
-  unsigned *slots = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
-  unsigned *cnt0 = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes +
-                                                kBpttSlotBytes);
+  unsigned *cnt0 = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
   auto counter = [&](int64_t t, int tb) { return cnt0 + (t * tl.nbt + tb) * 16; };
 
-  int blk = (int)blockIdx.x;
-  if (tl.xcd) {
-    __shared__ int s_role;
-    if (tid == 0) {
-      const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15);
-      s_role = -1;
-      if (xcc < tl.nbt) {
-        const unsigned k = __hip_atomic_fetch_add(slots + xcc * 16, 1u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-        if (k < (unsigned)tl.nut) s_role = xcc * tl.nut + (int)k;
-      }
-    }
-    __syncthreads();
-    if (s_role < 0) return;
-    blk = s_role;
-  }
+  const int blk = (int)blockIdx.x;
   const int tb = blk / tl.nut, tu = blk % tl.nut;
   const int64_t b0 = (int64_t)tb * tl.bB, j0 = (int64_t)tu * tl.u;
   const int nb = (int)std::min<int64_t>(tl.bB, B - b0);
@@ -316,19 +292,9 @@ static bool plan_bptt(const BpttArgs &a, int cus, int lds_max, BpttTiling *out) 
   // of the slice's da_{t+1}, so fewer, wider tiles move fewer bytes a step
   tl.u = (int)std::min<int64_t>(16, a.H);
   tl.nut = (int)((a.H + tl.u - 1) / tl.u);
-  // a slice per XCD when the chip is whole and a slice's tiles fit one XCD
-  // (the batch spread over all eight), else slices of 16 rows
-  tl.xcd = 0;
-  if (cus == kBpttXcds * kBpttXcdCus && tl.nut <= kBpttXcdCus) {
-    tl.bB = (int)std::min<int64_t>(16, (a.B + kBpttXcds - 1) / kBpttXcds);
-    tl.nbt = (int)((a.B + tl.bB - 1) / tl.bB);
-    tl.xcd = tl.nbt <= kBpttXcds;
-  }
-  if (!tl.xcd) {
-    tl.bB = (int)std::min<int64_t>(a.B, 16);
-    tl.nbt = (int)((a.B + tl.bB - 1) / tl.bB);
-  }
-  tl.grid = tl.xcd ? cus : tl.nbt * tl.nut;
+  tl.bB = (int)std::min<int64_t>(a.B, 16);
+  tl.nbt = (int)((a.B + tl.bB - 1) / tl.bB);
+  tl.grid = tl.nbt * tl.nut;
   if (tl.grid > cus) return false;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -346,10 +312,10 @@ static bool plan_bptt(const BpttArgs &a, int cus, int lds_max, BpttTiling *out) 
 }
 
 size_t bptt_ws(int64_t T, int64_t B) {
-  // per-XCD slot counters, then per-step, per-slice arrival counters (64
-  // bytes each; at most max(8, B / 16 rounded up) slices) after the header
-  const int64_t slices = std::max<int64_t>(8, (B + 15) / 16);
-  return kHeaderBytes + kBpttSlotBytes + (size_t)std::max<int64_t>(T, 1) * (size_t)slices * 64;
+  // per-step, per-slice arrival counters (64 bytes each) after the header, or
+  // the whole-chip layout's exchange
+  const int64_t slices = std::max<int64_t>(1, (B + 15) / 16);
+  return std::max(kHeaderBytes + (size_t)std::max<int64_t>(T, 1) * (size_t)slices * 64, xbptt_ws(B));
 }
 
 hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported) {
@@ -361,6 +327,9 @@ hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported) {
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
+  bool done = false;
+  e = launch_xbptt(a, cus, lds_max, s, &done);
+  if (e != hipSuccess || done) return e;
   BpttTiling tl;
   if (!plan_bptt(a, cus, lds_max, &tl)) {
     *unsupported = true;
@@ -376,7 +345,7 @@ hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported) {
     *unsupported = true;
     return hipSuccess;
   }
-  e = clear_exchange(a.ws, (int64_t)((bptt_ws(a.T, a.B) - kHeaderBytes) / 8), s);
+  e = clear_exchange(a.ws, a.T * tl.nbt * 8, s);
   if (e != hipSuccess) return e;
   BpttArgs args = a;
   void *kargs[] = {&args, &tl};

@@ -28,6 +28,15 @@ __device__ __forceinline__ void put_word(uint64_t *p, uint32_t tag, uint32_t v) 
                      __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// Two neighbouring words with one 16-byte store (p 16-byte aligned); readers
+// poll each word by its own tag.  The wait states keep the data registers
+// from being rewritten before a store of more than 8 bytes has read them,
+// which neither the hardware nor (inside an asm statement) the compiler checks.
+__device__ __forceinline__ void put_words2(uint64_t *p, uint32_t tag, uint32_t v0, uint32_t v1) {
+  const v4i w = {(int)v0, (int)tag, (int)v1, (int)tag};
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(w) : "memory");
+}
+
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 // Waits until every vector memory operation of the wave has completed (gfx9

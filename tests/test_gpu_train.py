@@ -129,3 +129,13 @@ def test_train_step_rejects_projection_layers(ql):
     w = random_model(8, 16, 1, proj=4, states=5, seed=1)
     cm = ql.CTrainModel(1, (ql.CTrainLayer * 1)(ql.CTrainLayer(8, 16, 4, 1, 1, 1, 1)), 5, 1, 1)
     assert ql.load().ql_train_step_workspace(cm, 3, 2, 4) == 0
+
+
+# The backward recurrence with an eighth of the batch per XCD, at its edges:
+# two frames; a tile of one cell; 1, 4, 5, 8 and 9 rows per XCD (the last XCDs
+# short or empty); one row more than a launch holds; every tile full.
+@pytest.mark.parametrize("H,T,B", [(16, 2, 4), (17, 6, 9), (33, 5, 32), (500, 4, 33), (500, 3, 64),
+                                   (36, 4, 65), (40, 3, 129), (512, 3, 7)])
+def test_train_backward_xcd_rows(ql, orc, H, T, B):
+    w, x, y = _case(24, H, 2, 40, T, B, seed=H + T + B)
+    _compare(ql, orc, w, x, y, lr=0.5, quantize_output=True)
