@@ -106,22 +106,21 @@ __device__ __forceinline__ bool poll_to_lds(uint32_t need, uint32_t tag, SrcFn s
   }
 }
 
-// The first round of poll_to_lds issued ahead of other work: the words
-// whose bit is set in `need` are loaded into w; poll_to_lds_finish examines
-// them later (and polls on for those whose tag had not matched).
+// The first round of poll_to_lds issued ahead of other work: every word is
+// loaded into w (src gives a valid address for each), without a branch, so
+// that waiting for them later leaves loads issued after them in flight;
+// poll_to_lds_finish examines them (and polls on for the words of `need` whose
+// tag had not matched).
 template <int N, class SrcFn>
-__device__ __forceinline__ void poll_to_lds_issue(uint32_t need, SrcFn src, uint64_t (&w)[N]) {
+__device__ __forceinline__ void poll_to_lds_issue_all(SrcFn src, uint64_t (&w)[N]) {
   int th = (int)threadIdx.x;
   asm volatile("" : "+v"(th));
 #pragma unroll
-  for (int i = 0; i < N; ++i) w[i] = ((need >> i) & 1u) ? ld_tagged(src(i, th)) : 0;
+  for (int i = 0; i < N; ++i) w[i] = ld_tagged(src(i, th));
 }
 template <int N, class SrcFn, class DstFn>
 __device__ __forceinline__ bool poll_to_lds_finish(uint32_t need, uint32_t tag, const uint64_t (&w)[N],
                                                    SrcFn src, DstFn dst, int *flag) {
-  // every load of the round has landed, on every path (they are the wave's
-  // youngest memory operations, so this waits for nothing more)
-  wait_vmcnt0();
   int th = (int)threadIdx.x;
   asm volatile("" : "+v"(th));
 #pragma unroll

@@ -79,19 +79,21 @@ def test_xcd_stack_repeats_bit_for_bit(ql):
         assert torch.equal(got["post"], ref["post"])
 
 
-# Row groups: 16 of them share the chip, up to 16 rows each, up to 32 when the
-# batch needs it, several launches beyond.  Batches at the edges of these.
+# Row groups of up to 16 rows: 16 of them share the chip with 32-cell tiles, 32
+# with 64-cell tiles, several launches beyond.  Batches at the edges of these.
 GROUP_CASES = [
     (2, 40, 48, 6, 2),       # the smallest batch
     (5, 40, 36, 5, 15),      # one group per layer, one row short
-    (8, 24, 64, 5, 33),      # 2 groups of 32 rows at most: 17 + 16
-    (3, 24, 100, 4, 65),     # 5 groups of 13 rows
-    (5, 40, 48, 4, 49),      # one row more than 3 groups of 16 hold
+    (5, 40, 36, 2, 48),      # the most rows of 5 layers in 32-cell tiles
+    (5, 40, 48, 4, 49),      # one row more: 64-cell tiles, 4 groups of 13
+    (8, 24, 64, 5, 33),      # 2 groups of 16 at most: 64-cell tiles, 3 of 11
+    (3, 24, 100, 4, 65),     # 5 groups of 13 rows; tiles without cells
     (5, 40, 500, 3, 97),     # one row more than a launch holds: 49 + 48
     (4, 512, 512, 2, 128),   # a full launch at the widest
-    (3, 320, 260, 3, 190),   # two launches of 3 groups of 32
+    (3, 320, 260, 3, 190),   # two launches of 6 groups
     (5, 24, 16, 3, 150),     # narrow cells: the scratch holds fewer groups
     (9, 24, 32, 3, 20),      # more layers than one launch holds: 5 + 4
+    (3, 40, 130, 1, 60),     # one frame in 64-cell tiles
 ]
 
 
