@@ -113,6 +113,7 @@ hipError_t set_wait_bound_f32(int polls);
 hipError_t set_wait_bound_train(int polls);
 hipError_t set_wait_bound_xrec(int polls);
 hipError_t set_wait_bound_xstack(int polls);
+hipError_t set_wait_bound_xrow(int polls);
 hipError_t set_wait_bound_xf32(int polls);
 hipError_t set_wait_bound_xbptt(int polls);
 // Reads the timeout flag a persistent launch left in its workspace (syncs s).
@@ -192,6 +193,11 @@ size_t xstack_ws(int nl);
 bool xstack_shapes(int nl, int64_t B, int64_t H, int64_t in0, int64_t in1, size_t ws_bytes, int cus,
                    int lds_max);
 bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max);
+// One batch row on the whole chip (ql_xrow.hip): one XCD per layer.  *done as above.
+hipError_t launch_xrow(const StackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
+                       bool *done);
+hipError_t launch_xrow(const PStackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
+                       bool *done);
 hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,
                          hipStream_t s, bool *done);
 // 1 when launch_stack would run a in that layout at batch 16 to 64 on the

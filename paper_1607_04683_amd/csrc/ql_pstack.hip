@@ -1,7 +1,8 @@
 // ql_pstack.hip -- stacked LSTM layers with a linear projection after each
 // (Section 4: 5 x 500 cells with P = 100 .. 400 projection units) at one batch
 // row, all in one persistent launch run as a wavefront: while layer l works on
-// frame t, layer l-1 is already on a later frame.
+// frame t, layer l-1 is already on a later frame.  This is the layout of a
+// partition of the chip; the whole chip runs ql_xrow.hip.
 //
 // A tile owns u cells of one layer (the 4u gate rows of W_x' and W_h', resident
 // in LDS) and v rows of the layer's projection W_r' (also resident).  Per
@@ -387,6 +388,14 @@ hipError_t launch_pstack(const PStackArgs &a, hipStream_t s, bool *unsupported) 
   for (int l = 0; l < a.nl; ++l) {
     const PStackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.acc_r || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
+  }
+  {
+    // the whole chip: one XCD per layer
+    int64_t hs[kMaxStack], ps[kMaxStack];
+    for (int l = 0; l < a.nl; ++l) hs[l] = a.L[l].H, ps[l] = a.L[l].P;
+    bool done = false;
+    const hipError_t e = launch_xrow(a, pstack_ws(hs, ps, a.nl, a.T), cus, tp, s, &done);
+    if (e != hipSuccess || done) return e;
   }
   auto kern = tp ? k_pstack<true> : k_pstack<false>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),

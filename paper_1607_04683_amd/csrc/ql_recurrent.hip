@@ -712,6 +712,7 @@ hipError_t set_wait_bound(int polls) {
     if (e == hipSuccess) e = set_wait_bound_train(polls);
     if (e == hipSuccess) e = set_wait_bound_xrec(polls);
     if (e == hipSuccess) e = set_wait_bound_xstack(polls);
+    if (e == hipSuccess) e = set_wait_bound_xrow(polls);
     if (e == hipSuccess) e = set_wait_bound_xf32(polls);
     if (e == hipSuccess) e = set_wait_bound_xbptt(polls);
   }

@@ -26,6 +26,9 @@
 // the tagged h words until every tag matches, quantize, store the codes with
 // device-coherent stores and then bump the slice's arrival counter, which
 // the unit tiles and the next layer wait on.
+// This is the layout of a partition of the chip and of wider inputs; the whole
+// chip runs one row in ql_xrow.hip and more in ql_xstack.hip.
+//
 // Between layers nothing is reused: codes go to full-length [T*B] buffers,
 // so a layer may run any number of steps ahead of the next one; a layer
 // never waits on a later layer.
@@ -39,7 +42,6 @@
 namespace ql {
 
 constexpr int kStackThreads = 512;
-constexpr int kXcds = 8;  // accelerator complex dies (XCDs) of the MI355X, each with its own L2
 constexpr int kXcdCus = 32;  // CUs of one XCD
 // Replicas of the tagged h words at one batch row (readers spread over them).
 constexpr int kMaxReph = 2;
@@ -55,7 +57,6 @@ struct StackTiling {
   int ldXmax;               // largest padded input width over the launch
   int ldsW, ldsWx, ldsX, ldsXx;
   int reph;                 // replicas of the tagged h buffer (one batch row per tile)
-  int xcd;                  // one-row tiles: every layer's tiles on one XCD of its own
   int64_t strideh;          // 64-bit words between replicas
   int nw;                   // tagged code words per row: ldH / 4 codes + 3 params
   size_t hx_bytes, cx_bytes, layer_bytes;  // exchange bytes per layer
@@ -91,23 +92,7 @@ __global__ __launch_bounds__(kStackThreads) void k_stack(StackArgs a, StackTilin
   const int64_t T = a.T, B = a.B, H = a.H;
   int *flag = reinterpret_cast<int *>(a.ws) + kHdrFlag;
   unsigned *cnt0 = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
-  // XCD-local layout: the launch has a workgroup for every CU; each takes the
-  // next free slot of the XCD it runs on (XCC_ID) and plays tile `slot` of
-  // layer `xcc`, so a layer's tiles share one L2 (the per-layer counters,
-  // unused at one batch row, hand out the slots); the rest leave at once.
-  int blk = (int)blockIdx.x;
-  if (tl.xcd) {
-    __shared__ int s_role;
-    if (threadIdx.x == 0) {
-      const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15);
-      const unsigned k = __hip_atomic_fetch_add(cnt0 + xcc * 16, 1u, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-      s_role = xcc < a.nl && k < (unsigned)tl.gl ? xcc * tl.gl + (int)k : -1;
-    }
-    __syncthreads();
-    if (s_role < 0) return;
-    blk = s_role;
-  }
+  const int blk = (int)blockIdx.x;
   const int l = blk / tl.gl, wgi = blk % tl.gl;
   const StackLayer &Ly = a.L[l];
   const int64_t IN = Ly.in;
@@ -324,10 +309,8 @@ __global__ __launch_bounds__(kStackThreads) void k_stack(StackArgs a, StackTilin
       const float cn = (fg * cst[lb * tl.u + jj]) + (ig * gv);
       cst[lb * tl.u + jj] = cn;
       const float m = og * tanh_cw(cn);
-      for (int c2 = 0; c2 < tl.reph; ++c2) {
-        if (tl.xcd) publish_local(&xht[c2 * tl.strideh + hcur + b * H + j], (uint32_t)(t + 1), m);
-        else publish(&xht[c2 * tl.strideh + hcur + b * H + j], (uint32_t)(t + 1), m);
-      }
+      for (int c2 = 0; c2 < tl.reph; ++c2)
+        publish(&xht[c2 * tl.strideh + hcur + b * H + j], (uint32_t)(t + 1), m);
       if (Ly.h) Ly.h[(t * B + b) * H + j] = m;
       if constexpr (TP) {
         if (Ly.tap_gates) {
@@ -860,15 +843,6 @@ static bool plan_stack_bb(const StackArgs &a, int cus, int lds_max, int bB, Stac
   tl.gl = tl.nbt * (tl.nut + tl.nq);
   tl.grid = a.nl * tl.gl;
   if (tl.grid > cus) return false;
-  // one-row tiles: each layer on an XCD of its own when its tiles fit one
-  // (the h exchange then stays in that XCD's L2); the grid covers every CU.
-  // Only on the whole chip (all eight XCDs, XCC_IDs 0..7): a partition of it
-  // keeps the spread layout.
-  tl.xcd = 0;
-  if (bB == 1 && cus == kXcds * kXcdCus && a.nl <= kXcds && tl.gl <= kXcdCus) {
-    tl.xcd = 1;
-    tl.grid = cus;
-  }
   const int nrows = 4 * tl.u;
   // LDS layout
   size_t off = 0;
@@ -974,8 +948,10 @@ hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
-  // two or more batch rows on the whole chip: row groups on XCDs of their own
+  // on the whole chip: one batch row with an XCD per layer, more as row groups
+  // on XCDs of their own
   bool done = false;
+  if (a.B == 1) e = launch_xrow(a, stack_ws(a.nl, a.T, a.B, a.H), cus, tp, s, &done);
   if (a.B > 1) e = launch_xstack(a, stack_ws(a.nl, a.T, a.B, a.H), cus, lds_max, tp, s, &done);
   if (e != hipSuccess || done) return e;
   StackTiling tl;
