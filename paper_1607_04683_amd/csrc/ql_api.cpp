@@ -364,6 +364,7 @@ PStackArgs pstack_shape_args(const ql_lstm_layer *layers, int n, int64_t T) {
   PStackArgs a{};
   a.nl = n < kMaxStack ? n : kMaxStack;
   a.T = T;
+  a.B = 1;
   for (int k = 0; k < a.nl; ++k) {
     a.L[k].in = layers[k].in;
     a.L[k].H = layers[k].hidden;
@@ -406,6 +407,35 @@ PStackLayer pstack_layer(const ql_lstm_layer &L, const ActRows &xin, const ActBu
   s.hT = st_hout(s1, l);
   s.cT = st_cout(s1, l);
   return s;
+}
+
+// Layers that all have a projection, at two or more batch rows, run as row
+// groups of the whole chip where their exchange fits the space of W_x x + b,
+// which that layout does not form.  *done false: one layer per launch.
+ql_status run_proj_rows(const ql_model &M, const ActRows &xin, const ActBuf &last, int64_t T, int64_t B,
+                        void *ws, void *words, size_t word_bytes, const ql_model_taps *taps,
+                        const ql_lstm_state *s0, const ql_lstm_state *s1, hipStream_t s, bool *done) {
+  *done = false;
+  if (B < 2 || M.nlayers < 2 || M.nlayers > kMaxStack) return QL_OK;
+  PStackArgs a{};
+  a.nl = M.nlayers;
+  a.T = T;
+  a.B = B;
+  a.ws = ws;
+  bool tp = false;
+  for (int l = 0; l < M.nlayers; ++l) {
+    if (M.layers[l].proj <= 0) return QL_OK;
+    const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l] : nullptr;
+    const bool top = l == M.nlayers - 1;
+    a.L[l] = pstack_layer(M.layers[l], l == 0 ? xin : ActRows{}, top ? last : ActBuf{}, lt, s0, s1, l);
+    const PStackLayer &L = a.L[l];
+    tp = tp || L.acc_x || L.acc_h || L.acc_r || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
+  }
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return QL_EHIP;
+  return from_hip(launch_xrows(a, words, word_bytes, cus, tp, s, done));
 }
 
 // Workspace of a model forward: exchange scratch first (it holds the timeout
@@ -564,7 +594,16 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   } else if (pst) {
     per_launch = pstack_per_launch(M->layers, M->nlayers, T, B);
   }
-  for (int l = 0; l < M->nlayers;) {
+  bool whole = false;
+  if (!stack && !pst) {
+    ActBuf last = mw.out[0];
+    last.ld = round_up(layer_width(M->layers[M->nlayers - 1]), 64);
+    st = run_proj_rows(*M, cur, last, T, B, mw.rec, mw.gx, (size_t)(MB * 4 * maxH) * sizeof(float), taps,
+                       s0, s1, s, &whole);
+    if (st != QL_OK) return st;
+    if (whole) cur = last.rows();
+  }
+  for (int l = whole ? M->nlayers : 0; l < M->nlayers;) {
     const int left = M->nlayers - l;
     // split the layers into launches of nearly equal size
     const int launches = (left + per_launch - 1) / per_launch;
@@ -592,6 +631,7 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
       PStackArgs pa{};
       pa.nl = n;
       pa.T = T;
+      pa.B = 1;
       pa.ws = mw.rec;
       for (int k = 0; k < n; ++k) {
         const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l + k] : nullptr;
@@ -942,6 +982,7 @@ ql_status ql_lstm_stack_forward(const ql_lstm_layer *layers, int32_t n, const ql
     PStackArgs pa{};
     pa.nl = n;
     pa.T = T;
+    pa.B = 1;
     pa.ws = ws;
     for (int k = 0; k < n; ++k) {
       const ActRows xin = k == 0 ? ActRows{x->codes, x->ld, x->zero, x->inv_q, x->sums} : ActRows{};

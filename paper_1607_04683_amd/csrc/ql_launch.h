@@ -114,12 +114,15 @@ hipError_t set_wait_bound_train(int polls);
 hipError_t set_wait_bound_xrec(int polls);
 hipError_t set_wait_bound_xstack(int polls);
 hipError_t set_wait_bound_xrow(int polls);
+hipError_t set_wait_bound_xrows(int polls);
 hipError_t set_wait_bound_xf32(int polls);
 hipError_t set_wait_bound_xbptt(int polls);
 // Reads the timeout flag a persistent launch left in its workspace (syncs s).
 hipError_t recurrent_timed_out(const void *ws, hipStream_t s, bool *timed_out);
 // Zeroes the n64 64-bit words after the workspace header (counters first).
 hipError_t clear_exchange(void *ws, int64_t n64, hipStream_t s);
+// The same, and the m64 words at `extra`, in one launch.
+hipError_t clear_exchange2(void *ws, int64_t n64, uint64_t *extra, int64_t m64, hipStream_t s);
 
 // ---- several stacked layers in one launch (ql_stack.hip)
 constexpr int kMaxStack = 8;
@@ -175,12 +178,19 @@ struct PStackLayer {
 };
 struct PStackArgs {
   int nl;                  // layers in this launch (1 .. kMaxStack)
-  int64_t T;               // frames (batch 1)
+  int64_t T, B;            // frames, batch rows (1 in k_pstack)
   PStackLayer L[kMaxStack];
   void *ws;                // pstack_ws bytes; timeout flag cleared by the caller
 };
 size_t pstack_ws(const int64_t *H, const int64_t *P, int nl, int64_t T);
 hipError_t launch_pstack(const PStackArgs &a, hipStream_t s, bool *unsupported);
+// A few batch rows a group on the whole chip (ql_xrows.hip), the words of
+// exchange in `words`.  A layer without out.codes writes no output (the next
+// layer of the launch takes its codes through the exchange).  *done false when
+// the shapes, the scratch or the device do not fit that layout (nothing
+// launched).
+hipError_t launch_xrows(const PStackArgs &a, void *words, size_t word_bytes, int cus, bool taps,
+                        hipStream_t s, bool *done);
 // How many of a.nl layers fit one launch (1: none; use the one-layer path).
 int pstack_layers_per_launch(const PStackArgs &a);
 
@@ -198,6 +208,9 @@ hipError_t launch_xrow(const StackArgs &a, size_t ws_bytes, int cus, bool taps, 
                        bool *done);
 hipError_t launch_xrow(const PStackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
                        bool *done);
+// A few rows (ql_xrows.hip): one XCD per layer and row group.  *done as above.
+hipError_t launch_xrows(const StackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
+                        bool *done);
 hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,
                          hipStream_t s, bool *done);
 // 1 when launch_stack would run a in that layout at batch 16 to 64 on the

@@ -685,6 +685,19 @@ hipError_t clear_exchange(void *ws, int64_t n64, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ void k_clear_exchange2(uint64_t *x, int64_t n64, uint64_t *y, int64_t m64) {
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n64 + m64;
+       k += (int64_t)gridDim.x * blockDim.x)
+    *(k < n64 ? x + k : y + (k - n64)) = 0;
+}
+hipError_t clear_exchange2(void *ws, int64_t n64, uint64_t *extra, int64_t m64, hipStream_t s) {
+  const unsigned zb = (unsigned)std::min<int64_t>(1024, (n64 + m64 + 255) / 256 + 1);
+  hipLaunchKernelGGL(k_clear_exchange2, dim3(zb), dim3(256), 0, s,
+                     reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + kHeaderBytes), n64, extra,
+                     m64);
+  return hipGetLastError();
+}
+
 hipError_t reset_recurrent_flag(void *ws, hipStream_t s) {
   hipLaunchKernelGGL(k_clear_exchange, dim3(1), dim3(64), 0, s, static_cast<unsigned *>(ws),
                      (int64_t)0, 1);
@@ -713,6 +726,7 @@ hipError_t set_wait_bound(int polls) {
     if (e == hipSuccess) e = set_wait_bound_xrec(polls);
     if (e == hipSuccess) e = set_wait_bound_xstack(polls);
     if (e == hipSuccess) e = set_wait_bound_xrow(polls);
+    if (e == hipSuccess) e = set_wait_bound_xrows(polls);
     if (e == hipSuccess) e = set_wait_bound_xf32(polls);
     if (e == hipSuccess) e = set_wait_bound_xbptt(polls);
   }

@@ -27,7 +27,7 @@
 // device-coherent stores and then bump the slice's arrival counter, which
 // the unit tiles and the next layer wait on.
 // This is the layout of a partition of the chip and of wider inputs; the whole
-// chip runs one row in ql_xrow.hip and more in ql_xstack.hip.
+// chip runs one row in ql_xrow.hip, a few in ql_xrows.hip and more in ql_xstack.hip.
 //
 // Between layers nothing is reused: codes go to full-length [T*B] buffers,
 // so a layer may run any number of steps ahead of the next one; a layer
@@ -948,10 +948,12 @@ hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
-  // on the whole chip: one batch row with an XCD per layer, more as row groups
-  // on XCDs of their own
+  // on the whole chip: one batch row, or up to eight per group, with an XCD per
+  // layer; more as units of 16
   bool done = false;
   if (a.B == 1) e = launch_xrow(a, stack_ws(a.nl, a.T, a.B, a.H), cus, tp, s, &done);
+  if (a.B > 1) e = launch_xrows(a, stack_ws(a.nl, a.T, a.B, a.H), cus, tp, s, &done);
+  if (e != hipSuccess || done) return e;
   if (a.B > 1) e = launch_xstack(a, stack_ws(a.nl, a.T, a.B, a.H), cus, lds_max, tp, s, &done);
   if (e != hipSuccess || done) return e;
   StackTiling tl;
