@@ -11,9 +11,10 @@
 // and hands every other workgroup the partial sums of that one's 16 cells:
 // 32 KB of tagged words written and read a step.  The 64 rows of W_h stay in
 // registers (wave w the cells [64 w, 64 w + 64) as outputs, one register per
-// k); products are v_mfma_f32_4x4x1_16b_f32, 16 blocks of four output cells x
-// four batch rows, so 4 rows are the unit of padding and no sum crosses
-// waves before it is published.  A step t = T-1 .. 0:
+// k); products are v_mfma_f32_4x4x1_16b_f32, 16 blocks of four batch rows x
+// four output cells, the rows broadcast from one block to all (one register
+// of da serves 16 steps of k), so 4 rows are the unit of padding and no sum
+// crosses waves before it is published.  A step t = T-1 .. 0:
 //   1. the partial sums of W_h^T da_{t+1} for this tile's (row, cell) pairs:
 //      four threads a pair, each polls and adds the words of eight tiles in
 //      tile order, then the four add up;
@@ -50,8 +51,9 @@ struct XbTiling {
   int rows;        // rows per XCD (the last may hold fewer or none)
 };
 
-// Exchange words of one XCD: [2 parities][dst tile][src tile][row][16 words, a
-// cell each].
+// Exchange words of one XCD: [2 parities][dst tile][src tile][row pair][16
+// cells][2 rows]: the 16-byte stores of 16 lanes, a cell's two rows each, are
+// contiguous.
 template <int NG>
 struct XbLay {
   static constexpr int64_t src = 4 * NG * kXbCells;
@@ -109,17 +111,16 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
   for (int i = tid; i < 2 * NR * kXbLdx; i += kXbThreads) xs[i] = 0.0f;  // rows and cells past the end
 
   // (pair, gate) values q = tid + 512 r: gate q & 3 (also: the eighth of the
-  // tiles whose partial sums the thread adds) of pair q >> 2, which is word
-  // pair & 15 of row pair >> 4; words hold cells in the order 0 1 4 5 8 9 12 13
-  // 2 3 6 7 .., so that the 16-byte stores of four lanes with two neighbouring
-  // cells each fill 64 bytes
-  const int gate = tid & 3, cell = ((tid >> 5) & 1) * 2 + ((tid >> 2) & 1) + ((tid >> 3) & 3) * 4;
+  // tiles whose partial sums the thread adds) of pair q >> 2, in the order of the
+  // exchange words: row 2 (pair >> 5) + (pair & 1), cell (pair >> 1) & 15
+  const int gate = tid & 3, cell = (tid >> 3) & 15;
+  auto row_of = [&](int r) { return 2 * ((tid + kXbThreads * r) >> 7) + ((tid >> 2) & 1); };
   const int64_t jc = j0 + cell;
   int64_t brow[NQ];
   bool live[NQ];
 #pragma unroll
   for (int r = 0; r < NQ; ++r) {
-    const int lb = (tid + kXbThreads * r) >> 6;
+    const int lb = row_of(r);
     live[r] = lb < nb && jc < H;
     brow[r] = live[r] ? b0 + lb : b0;
   }
@@ -156,9 +157,8 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
     for (int i = 0; i < 8; ++i)
       if (live[r] && 8 * gate + i < ntile) need |= 1u << (8 * r + i);
   uint64_t *Xin = X + tile * L::dst + 8 * gate * L::src;  // + par, + i * src, + pair
-  // where the wave's results go: tile 4 wave + (lane >> 4), cells 4 ((lane >> 2) & 3) .. + 3
-  uint64_t *Xout = X + (4 * wave + (lane >> 4)) * L::dst + tile * L::src + (lane & 3) * kXbCells +
-                   2 * ((lane >> 2) & 3);
+  // where the wave's results go: tile 4 wave + (lane >> 4), cell lane & 15
+  uint64_t *Xout = X + (4 * wave + (lane >> 4)) * L::dst + tile * L::src + 2 * (lane & 15);
   const bool out_ok = 64 * wave + 16 * (lane >> 4) < H;
   if (tile == 0) straggle_under_wait_bound();
   __syncthreads();
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
                                   : d_o * og * (1.0f - og);
       if (live[r]) {
         a.da[((t * B + brow[r]) * 4 + gate) * H + jc] = v;
-        xt[((tid + kXbThreads * r) >> 6) * kXbLdx + 4 * cell + gate] = v;
+        xt[row_of(r) * kXbLdx + 4 * cell + gate] = v;
       }
     }
 #pragma unroll
@@ -224,19 +224,19 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int n = 0; n < NA; ++n) acc[g][n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    const float *xr = xt + (lane & 3) * kXbLdx;
+    // lane 4 b + i holds da of row i at k = b of each 16
+    float d[NG][4];
 #pragma unroll
-    for (int k4 = 0; k4 < 16; ++k4) {
-      v4f d[NG];
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-      for (int g = 0; g < NG; ++g) d[g] = *reinterpret_cast<const v4f *>(xr + 4 * g * kXbLdx + 4 * k4);
+      for (int c = 0; c < 4; ++c) d[g][c] = xt[(4 * g + (lane & 3)) * kXbLdx + 16 * c + (lane >> 2)];
+    static_for<0, 64>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int g = 0; g < NG; ++g)
-          acc[g][k % NA] =
-              __builtin_amdgcn_mfma_f32_4x4x1f32(w[4 * k4 + k], d[g][k], acc[g][k % NA], 0, 0, 0);
-    }
+      for (int g = 0; g < NG; ++g)
+        acc[g][k % NA] =
+            __builtin_amdgcn_mfma_f32_4x4x1f32(d[g][k / 16], w[k], acc[g][k % NA], 4, k % 16, 0);
+    });
     const uint32_t tag = (uint32_t)(T - t + 1);
     uint64_t *dst = Xout + ((t - 1) & 1) * L::par;
 #pragma unroll
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
       if (out_ok)
 #pragma unroll
         for (int i = 0; i < 4; i += 2)
-          put_words2(dst + 4 * g * kXbCells + 4 * i, tag, __float_as_uint(s[i]), __float_as_uint(s[i + 1]));
+          put_words2(dst + (4 * g + i) * kXbCells, tag, __float_as_uint(s[i]), __float_as_uint(s[i + 1]));
     }
   }
 }

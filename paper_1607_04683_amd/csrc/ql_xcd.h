@@ -7,7 +7,19 @@
 #include "ql_device.h"
 #include "ql_exchange.h"
 
+#include <type_traits>
+
 namespace ql {
+
+// Calls f(integral_constant<int, I>) for I in [B, E): loops whose index an
+// instruction takes as an immediate.
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
 
 // n rounded up to 16 bytes (LDS layouts fixed at compile time)
 constexpr size_t xal16(size_t n) { return (n + 15) / 16 * 16; }

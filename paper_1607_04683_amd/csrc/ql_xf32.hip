@@ -7,9 +7,11 @@
 // registers for the launch, K split over its eight waves (64 floats of each of
 // the 64 rows, one register per k), so a step reads nothing but h_{t-1}.
 // Products are v_mfma_f32_4x4x1_16b_f32: its 16 blocks are the 16 cells, a
-// block's four rows the cell's gates i f g o, its four columns batch rows.
+// block's four rows batch rows, its four columns the cell's gates i f g o.
 // With at most 8 rows per XCD at batch 64, the 16-row shapes would multiply
-// as much padding as data; here 4 rows are the unit.  A step:
+// as much padding as data; here 4 rows are the unit.  The row operand is
+// broadcast from one block to all, so one register holds h for 16 steps of k.
+// A step:
 //   1. h_{t-1} of the XCD's rows, 64-bit words (step tag << 32 | fp32) that
 //      every tile polls from the L2, to LDS;
 //   2. the partial products of each wave's slice of K, to LDS;
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(kXfThreads) void k_xrec_f32(F32RecArgs a, XfTiling 
   constexpr int NA = NG == 1 ? 4 : NG == 2 ? 2 : 1;  // accumulators per row group
   constexpr int NQ = (256 * NG + kXfThreads - 1) / kXfThreads;  // gate values per thread
   float *xs = reinterpret_cast<float *>(smem);         // [NR][kXfLdx] h_{t-1}
-  float *part = xs + NR * kXfLdx;                      // [waves][NG][64 lanes][4 gates]
+  float *part = xs + NR * kXfLdx;                      // [waves][NG][16 cells][4 gates][4 rows]
 
   const int64_t T = a.T, B = a.B, H = a.H;
   if (threadIdx.x == 0) {
@@ -144,21 +146,21 @@ __global__ __launch_bounds__(kXfThreads) void k_xrec_f32(F32RecArgs a, XfTiling 
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int n = 0; n < NA; ++n) acc[g][n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    const float *xr = xs + (lane & 3) * kXfLdx + kw;
+    // lane 4 b + i holds h of row i at k = b of each 16
+    float h[NG][4];
 #pragma unroll
-    for (int k4 = 0; k4 < 16; ++k4)
-      if (4 * k4 < kpw) {
-        v4f h[NG];
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        h[g][c] = xs[(4 * g + (lane & 3)) * kXfLdx + kw + 16 * c + (lane >> 2)];
+    static_for<0, 64>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      if (k % 4 != 0 || k < kpw)  // (kpw is a multiple of 4: one test skips four)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-          h[g] = *reinterpret_cast<const v4f *>(xr + 4 * g * kXfLdx + 4 * k4);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-          for (int g = 0; g < NG; ++g)
-            acc[g][k % NA] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[4 * k4 + k], h[g][k],
-                                                                acc[g][k % NA], 0, 0, 0);
-      }
+          acc[g][k % NA] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[g][k / 16], w[k], acc[g][k % NA], 4,
+                                                              k % 16, 0);
+    });
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       // the results are read by ordinary instructions below: enough wait
@@ -181,7 +183,8 @@ __global__ __launch_bounds__(kXfThreads) void k_xrec_f32(F32RecArgs a, XfTiling 
       float sum = 0.0f;
       if (q < 256 * NG) {
 #pragma unroll
-        for (int v = 0; v < kXfWaves; ++v) sum += part[v * NG * 256 + q];
+        for (int v = 0; v < kXfWaves; ++v)
+          sum += part[(v * NG + (q >> 8)) * 256 + ((tid >> 4) & 15) * 16 + gate * 4 + ((q >> 2) & 3)];
       }
       const float av = gx[r] + sum;
       const float sg = sigmoid_cw(gate == 2 ? 2.0f * av : av);
