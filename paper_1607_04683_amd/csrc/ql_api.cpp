@@ -134,9 +134,20 @@ struct LayerWs {
   float *gx;       // [T*B][4H]
   ActBuf hout;     // codes of every h_t
 };
+// One layer that the whole-chip layouts of stacked layers take, as a stack of one.
+bool stack_of_one(const ql_lstm_layer &L) {
+  return L.proj == 0 && L.hidden <= 512 && L.in <= 512;
+}
+size_t stack_of_one_ws(const ql_lstm_layer &L, int64_t T, int64_t B) {
+  return std::max(stack_ws(1, T, B, L.hidden), B <= 32 ? xrows_ws(L.hidden, T, B) : 0);
+}
+StackLayer stack_layer(const ql_lstm_layer &L, const ActRows &xin, const ActBuf &out,
+                       const ql_lstm_taps *t, const ql_lstm_state *s0, const ql_lstm_state *s1, int l);
 LayerWs carve_layer(Carve &c, const ql_lstm_layer &L, int64_t T, int64_t B, bool quantize_input) {
   LayerWs w;
-  w.rec = c.take<char>(recurrent_ws(B, L.hidden, L.proj));
+  size_t rec = recurrent_ws(B, L.hidden, L.proj);
+  if (stack_of_one(L)) rec = std::max(rec, stack_of_one_ws(L, T, B));
+  w.rec = c.take<char>(rec);
   if (quantize_input) w.xin = take_act(c, T * B, L.in);
   w.gx = c.take<float>((size_t)(T * B * 4 * L.hidden));
   w.hout = take_act(c, T * B, layer_width(L));
@@ -326,6 +337,26 @@ ql_status ql_lstm_layer_forward(const ql_lstm_layer *L, const float *x, int64_t 
   if (launch_quantize_rows(x, L->in, T * B, L->in, w.xin.codes, w.xin.ld, w.xin.zero,
                            w.xin.inv_q, w.xin.sums, s) != hipSuccess)
     return QL_EHIP;
+  if (stack_of_one(*L)) {
+    // W_x x in the step, and no launch of its own and 16 bytes of it per cell and
+    // frame (a 500-cell layer, 200 frames, us before and so: 1 row 882 and 421, 8
+    // rows 965 and 525, 64 rows 2006 and 826, 256 rows 2433 and 848)
+    StackArgs a{};
+    a.nl = 1;
+    a.T = T;
+    a.B = B;
+    a.H = L->hidden;
+    a.ws = w.rec;
+    a.L[0] = stack_layer(*L, w.xin.rows(), w.hout, taps, nullptr, nullptr, 0);
+    a.L[0].h = h;
+    a.L[0].h0 = h0;
+    a.L[0].c0 = c0;
+    a.L[0].hT = hT;
+    a.L[0].cT = cT;
+    bool done = false;
+    if (launch_stack_chip(a, stack_of_one_ws(*L, T, B), s, &done) != hipSuccess) return QL_EHIP;
+    if (done) return QL_OK;
+  }
   return run_layer(*L, w.xin.rows(), T, B, h0, c0, h, hT, cT, w, taps, s);
 }
 

@@ -195,6 +195,9 @@ hipError_t launch_xrows(const PStackArgs &a, void *words, size_t word_bytes, int
 int pstack_layers_per_launch(const PStackArgs &a);
 
 hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported);
+// The whole-chip layouts of launch_stack alone, for one layer or more, with
+// ws_bytes of a.ws.  *done false when none of them fits (nothing launched).
+hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s, bool *done);
 // The same on the whole chip as independent row groups of 16 workgroups each
 // (ql_xstack.hip), over as many launches as the batch needs; ws_bytes of a.ws
 // may be used.  *done false when the shapes or the device do not fit that
@@ -209,6 +212,8 @@ hipError_t launch_xrow(const StackArgs &a, size_t ws_bytes, int cus, bool taps, 
 hipError_t launch_xrow(const PStackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
                        bool *done);
 // A few rows (ql_xrows.hip): one XCD per layer and row group.  *done as above.
+// xrows_ws: what one layer of H cells needs for T frames of B rows.
+size_t xrows_ws(int64_t H, int64_t T, int64_t B);
 hipError_t launch_xrows(const StackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
                         bool *done);
 hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,

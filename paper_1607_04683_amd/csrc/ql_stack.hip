@@ -930,13 +930,9 @@ int stack_layout(const StackArgs &a) {
              : 0;
 }
 
-hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
-  *unsupported = false;
-  if (a.T == 0 || a.B == 0) return hipSuccess;
-  if (a.nl < 1 || a.nl > kMaxStack || a.H > 512) {
-    *unsupported = true;
-    return hipSuccess;
-  }
+hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s, bool *done) {
+  *done = false;
+  if (a.T == 0 || a.B == 0 || a.nl < 1 || a.nl > kMaxStack || a.H > 512) return hipSuccess;
   int dev = 0, cus = 0, lds_max = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -948,14 +944,35 @@ hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
-  // on the whole chip: one batch row, or up to eight per group, with an XCD per
-  // layer; more as units of 16
+  // one batch row, or up to four per group, with an XCD per layer; more as
+  // units of 16
+  if (a.B == 1) return launch_xrow(a, ws_bytes, cus, tp, s, done);
+  e = launch_xrows(a, ws_bytes, cus, tp, s, done);
+  if (e != hipSuccess || *done) return e;
+  return launch_xstack(a, ws_bytes, cus, lds_max, tp, s, done);
+}
+
+hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
+  *unsupported = false;
+  if (a.T == 0 || a.B == 0) return hipSuccess;
+  if (a.nl < 1 || a.nl > kMaxStack || a.H > 512) {
+    *unsupported = true;
+    return hipSuccess;
+  }
   bool done = false;
-  if (a.B == 1) e = launch_xrow(a, stack_ws(a.nl, a.T, a.B, a.H), cus, tp, s, &done);
-  if (a.B > 1) e = launch_xrows(a, stack_ws(a.nl, a.T, a.B, a.H), cus, tp, s, &done);
+  hipError_t e = launch_stack_chip(a, stack_ws(a.nl, a.T, a.B, a.H), s, &done);
   if (e != hipSuccess || done) return e;
-  if (a.B > 1) e = launch_xstack(a, stack_ws(a.nl, a.T, a.B, a.H), cus, lds_max, tp, s, &done);
-  if (e != hipSuccess || done) return e;
+  int dev = 0, cus = 0, lds_max = 0;
+  e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  if (e != hipSuccess) return e;
+  bool tp = false;  // any tap or final state asked for
+  for (int l = 0; l < a.nl; ++l) {
+    const StackLayer &L = a.L[l];
+    tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
+  }
   StackTiling tl;
   if (!plan_stack(a, cus, lds_max, &tl)) {
     *unsupported = true;

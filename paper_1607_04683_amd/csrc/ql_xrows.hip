@@ -304,6 +304,10 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
             v[r][i] = init && lr < nb && k < n ? init[(b0 + lr) * n + k] : 0.0f;
           }
       } else {
+        // a round trip's worth of slack before the first read: with four rows most
+        // came too early (P = 200: 4.37 us a step at once, 4.26 so; with eight rows
+        // their loads take that long themselves)
+        if (RW == 1) __builtin_amdgcn_s_sleep(4);
         long it = 0;
         for (;;) {
           uint64_t w[RW][8];
@@ -568,6 +572,10 @@ static hipError_t launch_xrows_any(const Args &a, void *words, size_t word_bytes
   }
   *done = true;
   return hipSuccess;
+}
+
+size_t xrows_ws(int64_t H, int64_t T, int64_t B) {
+  return kHeaderBytes + kXvSlotBytes + 8 * (size_t)xv_words(H, H, false, T, B + kXvXcds);
 }
 
 hipError_t launch_xrows(const StackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
