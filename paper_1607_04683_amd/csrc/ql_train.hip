@@ -37,7 +37,15 @@ __global__ __launch_bounds__(256) void k_xent_grad(float *p, const int32_t *targ
 __global__ __launch_bounds__(256) void k_mean(const float *v, int64_t n, float *out) {
   __shared__ double part[256];
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) s += (double)v[i];
+  int64_t i = threadIdx.x;
+  for (; i + 15 * 256 < n; i += 16 * 256) {  // sixteen loads in flight
+    float x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = v[i + 256 * u];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += (double)x[u];
+  }
+  for (; i < n; i += 256) s += (double)v[i];
   part[threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -75,8 +83,17 @@ __global__ __launch_bounds__(256) void k_colsum_final(const float *part, int chu
                                                       float *out) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  float s = part[n];
-  for (int c = 1; c < chunks; ++c) s += part[(int64_t)c * N + n];
+  // sixteen chunks loaded before they are added (in order)
+  constexpr int kU = 16;
+  float s = 0.0f;
+  for (int c0 = 0; c0 < chunks; c0 += kU) {
+    float v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = part[(int64_t)(c0 + u < chunks ? c0 + u : 0) * N + n];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (c0 + u < chunks) s = c0 + u == 0 ? v[u] : s + v[u];
+  }
   out[n] = s;
 }
 
