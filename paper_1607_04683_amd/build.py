@@ -15,7 +15,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["ql_quantize.hip", "ql_gemm.hip", "ql_recurrent.hip", "ql_stack.hip", "ql_pstack.hip",
            "ql_f32.hip", "ql_xf32.hip", "ql_train.hip", "ql_xbptt.hip", "ql_xrec.hip", "ql_xstack.hip", "ql_xrow.hip", "ql_xrows.hip",
            "ql_api.cpp", "ql_scratch.hip"]
-HEADERS = ["ql_device.h", "ql_exchange.h", "ql_launch.h", "ql_rec_common.h", "ql_xcd.h"]
+HEADERS = ["ql_device.h", "ql_exchange.h", "ql_launch.h", "ql_quant_rows.h", "ql_rec_common.h", "ql_xcd.h"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -271,6 +271,10 @@ ql_status ql_quantized_matmul(const ql_qmatrix *W, const float *X, int64_t m, ql
   if (m < 0) return QL_ESHAPE;
   if (!ws || ws_bytes < ql_quantized_matmul_workspace(m, W->rows, W->cols)) return QL_EWORKSPACE;
   hipStream_t s = as_stream(stream);
+  bool done = false;
+  hipError_t es = launch_qmm_small(X, g == QL_ACT_PER_ROW, weight(*W), m, W->rows, W->cols, bias, Y, acc,
+                                   s, &done);
+  if (es != hipSuccess || done) return from_hip(es);
   Carve c(ws);
   ActBuf x = take_act(c, m, W->cols);
   void *qws = c.take<char>(set_quantize_ws(m, W->cols, 1));

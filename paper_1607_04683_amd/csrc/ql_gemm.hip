@@ -13,6 +13,7 @@
 // fragment reads of 32 consecutive rows spread over all banks.
 #include "ql_device.h"
 #include "ql_launch.h"
+#include "ql_quant_rows.h"
 
 namespace ql {
 
@@ -689,6 +690,57 @@ __global__ __launch_bounds__(64 * WM *WN) void k_gemm(const int8_t *__restrict__
     }
 }
 
+// The wave's results of few-row products: lane (fr, fq) holds columns nc .. + 3
+// (nc = n0 + 4 fq) of rows m0 + 16 b + fr; row(m) gives a row's params.
+struct SkinnyRow {
+  int32_t zero, sum;
+  float inv_q;
+};
+template <int MB, class RowFn>
+__device__ __forceinline__ void skinny_epilogue(const EpiArgs &e, int64_t M, int64_t N, int64_t K,
+                                                int64_t m0, int64_t nc, int fr, const v4i (&acc)[MB],
+                                                RowFn row) {
+  if (nc >= N) return;
+  int32_t ztw[4], sigw[4];
+  int64_t colterm[4];
+  float iqw[4], bn[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int64_t nn = nc + t < N ? nc + t : N - 1;
+    const int64_t blk = nn / e.w_rpb;
+    ztw[t] = e.w_zero[blk] + 128;
+    sigw[t] = e.w_sums[nn] - 128 * (int32_t)K;
+    colterm[t] = (int64_t)sigw[t] + K * (int64_t)ztw[t];
+    iqw[t] = e.w_inv_q[blk];
+    bn[t] = e.bias ? e.bias[nn] : 0.0f;
+  }
+  const bool vec = (N & 3) == 0;  // rows of Y and acc 16-byte aligned
+#pragma unroll
+  for (int b = 0; b < MB; ++b) {
+    const int64_t m = m0 + 16 * b + fr;
+    if (m >= M) continue;
+    const SkinnyRow r = row(m);
+    const int32_t sigx = r.sum - 128 * (int32_t)K, ztx = r.zero + 128;
+    const float iqx = r.inv_q;
+    float y[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      y[t] = recover(acc[b][t], colterm[t], ztw[t], ztx, sigx, iqw[t], iqx) + bn[t];
+    const int64_t off = m * N + nc;
+    if (vec && ((uintptr_t)e.Y & 15) == 0) {
+      *reinterpret_cast<float4 *>(e.Y + off) = make_float4(y[0], y[1], y[2], y[3]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (nc + t < N) e.Y[off + t] = y[t];
+    }
+    if (e.acc)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (nc + t < N) e.acc[off + t] = acc_u8(acc[b][t], sigw[t], sigx, K);
+  }
+}
+
 // Products of few rows (or few tiles): W' is what has to be read, so every
 // wave takes 16 of its rows, whole, straight into registers as MFMA fragments
 // (no LDS, no barrier), against MB 16-row blocks of X, whose codes the waves
@@ -736,46 +788,58 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_skinny(
       acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
           wf, *reinterpret_cast<const v4i *>(x[b] + c * 64), acc[b], 0, 0, 0);
   }
-  // lane: columns n0 + 4 fq .. + 3 of row m0 + 16 b + fr
-  const int64_t nc = n0 + 4 * fq;
-  if (nc >= N) return;
-  int32_t ztw[4], sigw[4];
-  int64_t colterm[4];
-  float iqw[4], bn[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int64_t nn = nc + t < N ? nc + t : N - 1;
-    const int64_t blk = nn / e.w_rpb;
-    ztw[t] = e.w_zero[blk] + 128;
-    sigw[t] = e.w_sums[nn] - 128 * (int32_t)K;
-    colterm[t] = (int64_t)sigw[t] + K * (int64_t)ztw[t];
-    iqw[t] = e.w_inv_q[blk];
-    bn[t] = e.bias ? e.bias[nn] : 0.0f;
+  skinny_epilogue<MB>(e, M, N, K, m0, n0 + 4 * fq, fr, acc, [&](int64_t m) {
+    return SkinnyRow{e.x_zero[m], e.x_sums[m], e.x_inv_q[m]};
+  });
+}
+
+// The product of small operands in one launch: every workgroup quantizes X
+// itself (per tensor, or per row), into LDS, and multiplies its 64 rows of W'.
+// At these sizes a launch costs more than reading X again (16 x 256 x 128 per
+// tensor: two launches 14.3 us a call, one 9.7).
+constexpr int kSmallValues = 8192, kSmallRows = 64;
+template <int MB, bool PER_ROW>
+__global__ __launch_bounds__(256) void k_qmm_small(const float *__restrict__ X, int64_t M,
+                                                   const int8_t *__restrict__ B, int64_t ldb, int64_t N,
+                                                   int64_t K, EpiArgs e) {
+  extern __shared__ __attribute__((aligned(16))) int8_t xs[];  // [M][round_up(K, 64) + 16]
+  __shared__ SkinnyRow rows[16 * MB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, fr = lane & 15, fq = lane >> 4;
+  const int nk = (int)((K + 63) / 64), ldx = 64 * nk + 16;
+  QParams p{};
+  if (!PER_ROW) {
+    float2 mm = range_minmax_block(X, M * K);
+    if (K == 0) mm = make_float2(0.0f, 0.0f);
+    p = make_qparams(mm.x, mm.y);
   }
-  const bool vec = (N & 3) == 0;  // rows of Y and acc 16-byte aligned
-#pragma unroll
-  for (int b = 0; b < MB; ++b) {
-    const int64_t m = m0 + 16 * b + fr;
-    if (m >= M) continue;
-    const int32_t sigx = e.x_sums[m] - 128 * (int32_t)K, ztx = e.x_zero[m] + 128;
-    const float iqx = e.x_inv_q[m];
-    float y[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      y[t] = recover(acc[b][t], colterm[t], ztw[t], ztx, sigx, iqw[t], iqx) + bn[t];
-    const int64_t off = m * N + nc;
-    if (vec && ((uintptr_t)e.Y & 15) == 0) {
-      *reinterpret_cast<float4 *>(e.Y + off) = make_float4(y[0], y[1], y[2], y[3]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (nc + t < N) e.Y[off + t] = y[t];
+  for (int m = wave; m < (int)M; m += 4) {
+    const DenseRow x{X + m * K};
+    if (PER_ROW) {
+      float2 mm = row_minmax_wave(x, K, lane);
+      if (K == 0) mm = make_float2(0.0f, 0.0f);
+      p = make_qparams(mm.x, mm.y);
     }
-    if (e.acc)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (nc + t < N) e.acc[off + t] = acc_u8(acc[b][t], sigw[t], sigx, K);
+    const int sum = encode_row_wave(x, K, xs + m * ldx, 64 * nk, p.q, p.z, lane);
+    if (lane == 0) rows[m] = SkinnyRow{p.z, sum, p.inv_q};
   }
+  __syncthreads();
+  const int64_t n0 = (int64_t)blockIdx.x * 64 + 16 * wave;
+  if (n0 >= N) return;
+  const int8_t *w = B + (n0 + fr < N ? n0 + fr : N - 1) * ldb + 16 * fq;
+  v4i acc[MB];
+#pragma unroll
+  for (int b = 0; b < MB; ++b) acc[b] = v4i{};
+#pragma unroll 8
+  for (int c = 0; c < nk; ++c) {
+    const v4i wf = *reinterpret_cast<const v4i *>(w + c * 64);
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      const int m = 16 * b + fr < (int)M ? 16 * b + fr : (int)M - 1;
+      acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+          wf, *reinterpret_cast<const v4i *>(xs + m * ldx + c * 64 + 16 * fq), acc[b], 0, 0, 0);
+    }
+  }
+  skinny_epilogue<MB>(e, M, N, K, 0, n0 + 4 * fq, fr, acc, [&](int64_t m) { return rows[m]; });
 }
 
 // Softmax of logit rows already in `post`, in place: one workgroup per row.
@@ -940,6 +1004,22 @@ hipError_t launch_gemm_recover(const ActRows &X, const WeightMat &W, int64_t M, 
   e.Y = Y;
   e.acc = acc;
   return dispatch<EPI_RECOVER>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);
+}
+
+hipError_t launch_qmm_small(const float *X, bool per_row, const WeightMat &W, int64_t M, int64_t N,
+                            int64_t K, const float *bias, float *Y, int32_t *acc, hipStream_t s,
+                            bool *done) {
+  *done = M > 0 && N > 0 && M <= kSmallRows && M * K <= kSmallValues;
+  if (!*done) return hipSuccess;
+  EpiArgs e = make_epi(ActRows{}, W, bias);
+  e.Y = Y;
+  e.acc = acc;
+  const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  auto kern = per_row ? (mb == 1 ? k_qmm_small<1, true> : mb == 2 ? k_qmm_small<2, true> : k_qmm_small<4, true>)
+                      : (mb == 1 ? k_qmm_small<1, false> : mb == 2 ? k_qmm_small<2, false> : k_qmm_small<4, false>);
+  const size_t lds = (size_t)M * (size_t)(round_up(K, 64) + 16);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((N + 63) / 64)), dim3(256), lds, s, X, M, W.codes, W.ld, N, K, e);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_raw(const int8_t *A, int64_t lda, const int8_t *B, int64_t ldb,

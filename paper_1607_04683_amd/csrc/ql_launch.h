@@ -53,6 +53,11 @@ struct WeightMat {
 hipError_t launch_gemm_recover(const ActRows &X, const WeightMat &W, int64_t M, int64_t N,
                                int64_t K, const float *bias, float *Y, int32_t *acc,
                                hipStream_t s);
+// The same of X [M][K] fp32, quantized per row or as one set, in one launch where
+// both are small.  *done false: too large (nothing launched).
+hipError_t launch_qmm_small(const float *X, bool per_row, const WeightMat &W, int64_t M, int64_t N,
+                            int64_t K, const float *bias, float *Y, int32_t *acc, hipStream_t s,
+                            bool *done);
 // C[m][n] = sum_k A'[m][k] B'[n][k] in the 0..255 domain.
 hipError_t launch_gemm_raw(const int8_t *A, int64_t lda, const int8_t *B, int64_t ldb,
                            int32_t *C, int64_t M, int64_t N, int64_t K, const int32_t *a_sums,

@@ -206,7 +206,8 @@ def _ptr(t):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # (the raw handle: a Stream object costs as much as a small call's launch)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ws(nbytes: int, device):
@@ -245,7 +246,8 @@ class QMatrix:
 
     @staticmethod
     def empty(rows: int, cols: int, nblocks: int, device) -> "QMatrix":
-        return QMatrix(torch.zeros(rows, ld_for(cols), dtype=torch.int8, device=device), rows,
+        # (the quantizer writes the rows' padding too)
+        return QMatrix(torch.empty(rows, ld_for(cols), dtype=torch.int8, device=device), rows,
                        cols, nblocks, torch.empty(nblocks, dtype=torch.float64, device=device),
                        torch.empty(nblocks, dtype=torch.int32, device=device),
                        torch.empty(nblocks, dtype=torch.float32, device=device),
