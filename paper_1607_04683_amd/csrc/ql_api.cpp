@@ -336,10 +336,9 @@ ql_status ql_lstm_layer_forward(const ql_lstm_layer *L, const float *x, int64_t 
   hipStream_t s = as_stream(stream);
   Carve c(ws);
   LayerWs w = carve_layer(c, *L, T, B, true);
-  if (reset_recurrent_flag(w.rec, s) != hipSuccess) return QL_EHIP;
-  if (T == 0 || B == 0) return QL_OK;
+  if (T == 0 || B == 0) return from_hip(reset_recurrent_flag(w.rec, s));
   if (launch_quantize_rows(x, L->in, T * B, L->in, w.xin.codes, w.xin.ld, w.xin.zero,
-                           w.xin.inv_q, w.xin.sums, s) != hipSuccess)
+                           w.xin.inv_q, w.xin.sums, s, recurrent_flag(w.rec)) != hipSuccess)
     return QL_EHIP;
   if (stack_of_one(*L)) {
     // W_x x in the step, and no launch of its own and 16 bytes of it per cell and
@@ -572,12 +571,12 @@ struct Frontend {
 };
 
 hipError_t quantize_input(const Frontend &f, int64_t T, int64_t B, int64_t in, const ActBuf &dst,
-                          hipStream_t s) {
+                          int *flag, hipStream_t s) {
   if (f.stacked)
     return launch_quantize_stacked(f.x, B, f.dim, f.stack, f.skip, T, dst.codes, dst.ld,
-                                   dst.zero, dst.inv_q, dst.sums, s);
+                                   dst.zero, dst.inv_q, dst.sums, s, flag);
   return launch_quantize_rows(f.x, in, T * B, in, dst.codes, dst.ld, dst.zero, dst.inv_q,
-                              dst.sums, s);
+                              dst.sums, s, flag);
 }
 
 ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_t B, float *post,
@@ -602,9 +601,9 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   }
   if (!ws || ws_bytes < ql_acoustic_model_workspace(M, T, B)) return QL_EWORKSPACE;
   hipStream_t s = as_stream(stream);
-  // the timeout flag sits at the start of the workspace in every forward call
-  if (reset_recurrent_flag(ws, s) != hipSuccess) return QL_EHIP;
-  if (T == 0 || B == 0) return QL_OK;
+  // the timeout flag sits at the start of the workspace in every forward call;
+  // the launch that quantizes the input clears it
+  if (T == 0 || B == 0) return from_hip(reset_recurrent_flag(ws, s));
 
   int64_t maxH = 0, maxR = 0, maxP = 0;
   for (int l = 0; l < M->nlayers; ++l) {
@@ -618,7 +617,8 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   Carve c(ws);
   ModelWs mw = carve_model(c, *M, T, B);
 
-  if (quantize_input(fe, T, B, M->layers[0].in, mw.xin, s) != hipSuccess) return QL_EHIP;
+  if (quantize_input(fe, T, B, M->layers[0].in, mw.xin, recurrent_flag(ws), s) != hipSuccess)
+    return QL_EHIP;
   ActRows cur = mw.xin.rows();
   const bool stack = stackable(*M);
   const bool pst = !stack && pstack_shapes(M->layers, M->nlayers, B);

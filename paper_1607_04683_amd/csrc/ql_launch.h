@@ -12,13 +12,15 @@ inline size_t align_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 inline int64_t round_up(int64_t n, int64_t a) { return (n + a - 1) / a * a; }
 
 // ---- quantizer (ql_quantize.hip)
+// flag (nullable): a word to clear in the same launch (the timeout flag of the
+// persistent launches that follow); m must not be 0 then.
 hipError_t launch_quantize_rows(const float *X, int64_t ldx, int64_t m, int64_t K, int8_t *codes,
                                 int64_t ld, int32_t *zero, float *inv_q, int32_t *sums,
-                                hipStream_t s);
+                                hipStream_t s, int *flag = nullptr);
 size_t set_quantize_ws(int64_t rows, int64_t cols, int nsets);
 hipError_t launch_quantize_stacked(const float *frames, int64_t B, int dim, int stack, int skip,
                                    int64_t T, int8_t *codes, int64_t ld, int32_t *zero,
-                                   float *inv_q, int32_t *sums, hipStream_t s);
+                                   float *inv_q, int32_t *sums, hipStream_t s, int *flag = nullptr);
 hipError_t launch_set_quantize(const float *X, int64_t rows, int64_t cols, int nsets, int8_t *codes,
                                int64_t ld, double *range, int32_t *zero, float *inv_q,
                                int32_t *row_sums, int32_t *row_zero, float *row_inv_q, void *ws,
@@ -108,6 +110,7 @@ int recurrent_layout(const RecurrentArgs &a);
 hipError_t launch_recurrent(const RecurrentArgs &a, hipStream_t s, bool *unsupported);
 // Clears the timeout flag (once per API call, before the first layer).
 hipError_t reset_recurrent_flag(void *ws, hipStream_t s);
+int *recurrent_flag(void *ws);
 // Bounds every wait of the persistent kernels to `polls` re-reads (0: the
 // default), on every device; one setter per source file with such kernels.
 hipError_t set_wait_bound(int polls);

@@ -44,9 +44,11 @@ __global__ __launch_bounds__(256) void k_quantize_rows(const float *__restrict__
                                                        int8_t *__restrict__ codes, int64_t ld,
                                                        int32_t *__restrict__ zero,
                                                        float *__restrict__ inv_q,
-                                                       int32_t *__restrict__ sums) {
+                                                       int32_t *__restrict__ sums,
+                                                       int *__restrict__ flag) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
+  if (flag && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
   if (row >= m) return;
   quantize_row_wave(DenseRow{X + row * ldx}, K, row, codes, ld, zero, inv_q, sums, lane);
 }
@@ -61,8 +63,10 @@ __global__ __launch_bounds__(256) void k_quantize_stacked(const float *__restric
                                                           int8_t *__restrict__ codes, int64_t ld,
                                                           int32_t *__restrict__ zero,
                                                           float *__restrict__ inv_q,
-                                                          int32_t *__restrict__ sums) {
+                                                          int32_t *__restrict__ sums,
+                                                          int *__restrict__ flag) {
   const int lane = threadIdx.x & 63;
+  if (flag && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
   const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
   if (row >= m) return;
   const int64_t t = row / B, b = row - t * B;
@@ -207,20 +211,20 @@ static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + p
 
 hipError_t launch_quantize_rows(const float *X, int64_t ldx, int64_t m, int64_t K, int8_t *codes,
                                 int64_t ld, int32_t *zero, float *inv_q, int32_t *sums,
-                                hipStream_t s) {
+                                hipStream_t s, int *flag) {
   if (m == 0) return hipSuccess;
   hipLaunchKernelGGL(k_quantize_rows, dim3(blocks_for(m, 4)), dim3(256), 0, s, X, ldx, m, K,
-                     codes, ld, zero, inv_q, sums);
+                     codes, ld, zero, inv_q, sums, flag);
   return hipGetLastError();
 }
 
 hipError_t launch_quantize_stacked(const float *frames, int64_t B, int dim, int stack, int skip,
                                    int64_t T, int8_t *codes, int64_t ld, int32_t *zero,
-                                   float *inv_q, int32_t *sums, hipStream_t s) {
+                                   float *inv_q, int32_t *sums, hipStream_t s, int *flag) {
   const int64_t m = T * B;
   if (m == 0) return hipSuccess;
   hipLaunchKernelGGL(k_quantize_stacked, dim3(blocks_for(m, 4)), dim3(256), 0, s, frames, B, dim,
-                     stack, skip, m, codes, ld, zero, inv_q, sums);
+                     stack, skip, m, codes, ld, zero, inv_q, sums, flag);
   return hipGetLastError();
 }
 

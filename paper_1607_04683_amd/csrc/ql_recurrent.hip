@@ -698,6 +698,8 @@ hipError_t clear_exchange2(void *ws, int64_t n64, uint64_t *extra, int64_t m64, 
   return hipGetLastError();
 }
 
+int *recurrent_flag(void *ws) { return static_cast<int *>(ws) + kHdrFlag; }
+
 hipError_t reset_recurrent_flag(void *ws, hipStream_t s) {
   hipLaunchKernelGGL(k_clear_exchange, dim3(1), dim3(64), 0, s, static_cast<unsigned *>(ws),
                      (int64_t)0, 1);
