@@ -600,14 +600,15 @@ hipError_t launch_recurrent_f32(const F32RecArgs &a, hipStream_t s, bool *unsupp
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
-  bool done = false;
-  e = launch_xrec_f32(a, cus, lds_max, s, &done);
-  if (e != hipSuccess || done) return e;
+  // the shapes taken are the same on every layout
   F32Tiling tl;
   if (!plan_f32(a, cus, lds_max, &tl)) {
     *unsupported = true;
     return hipSuccess;
   }
+  bool done = false;
+  e = launch_xrec_f32(a, cus, lds_max, s, &done);
+  if (e != hipSuccess || done) return e;
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_recurrent_f32),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)tl.lds_bytes);

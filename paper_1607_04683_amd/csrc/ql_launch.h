@@ -108,6 +108,8 @@ hipError_t launch_xrec(const RecurrentArgs &a, int cus, int lds_max, hipStream_t
 int recurrent_layout(const RecurrentArgs &a);
 // returns hipSuccess, or an error; *unsupported set if shapes do not fit.
 hipError_t launch_recurrent(const RecurrentArgs &a, hipStream_t s, bool *unsupported);
+// Whether the spread layout has a tiling for the shape.
+bool recurrent_fits(const RecurrentArgs &a, int cus, int lds_max);
 // Clears the timeout flag (once per API call, before the first layer).
 hipError_t reset_recurrent_flag(void *ws, hipStream_t s);
 int *recurrent_flag(void *ws);

@@ -924,6 +924,11 @@ static RecKernel pick_kernel(const RecurrentArgs &a, const RecTiling &tl) {
   return wideH ? k_recurrent<8, false, 32, false> : k_recurrent<8, false, 8, false>;
 }
 
+bool recurrent_fits(const RecurrentArgs &a, int cus, int lds_max) {
+  RecTiling tl;
+  return plan(a, cus, lds_max, &tl);
+}
+
 hipError_t launch_recurrent(const RecurrentArgs &a, hipStream_t s, bool *unsupported) {
   *unsupported = false;
   if (a.T == 0 || a.B == 0) return hipSuccess;

@@ -944,6 +944,14 @@ hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s,
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
+  // the batches taken are those of a launch per layer or of k_stack
+  if (a.B > 64) {
+    RecurrentArgs r{};
+    r.T = a.T, r.B = a.B, r.H = r.R = a.H;
+    if (!recurrent_fits(r, cus, lds_max) &&
+        stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.nl > 1 ? a.L[1].in : a.H) < 2)
+      return hipSuccess;
+  }
   // one batch row, or up to four per group, with an XCD per layer; more as
   // units of 16
   if (a.B == 1) return launch_xrow(a, ws_bytes, cus, tp, s, done);

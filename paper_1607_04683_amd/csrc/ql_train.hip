@@ -344,14 +344,15 @@ hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported) {
   if (e == hipSuccess)
     e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
-  bool done = false;
-  e = launch_xbptt(a, cus, lds_max, s, &done);
-  if (e != hipSuccess || done) return e;
+  // the shapes taken are the same on every layout
   BpttTiling tl;
   if (!plan_bptt(a, cus, lds_max, &tl)) {
     *unsupported = true;
     return hipSuccess;
   }
+  bool done = false;
+  e = launch_xbptt(a, cus, lds_max, s, &done);
+  if (e != hipSuccess || done) return e;
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_bptt),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)tl.lds_bytes);
   if (e != hipSuccess) return e;

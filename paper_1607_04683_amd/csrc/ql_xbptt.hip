@@ -26,7 +26,7 @@
 // its own polls of the first.  Bound by that chain: one hand-off (about 1 us)
 // and 128 MFMAs a wave (0.85 us at 8 rows).  A 500-cell layer at batch 64:
 // 8.75 us a step gathering da with device-coherent counters; 6.1 with single
-// words stored, 5.0 with two a store.
+// words stored, 5.0 with two a store, 4.7 with the rows broadcast.
 #include "ql_device.h"
 #include "ql_exchange.h"
 #include "ql_launch.h"

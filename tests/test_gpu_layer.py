@@ -37,3 +37,11 @@ def test_single_layer_equals_oracle(ql, orc, n_in, H, T, B):
         if k in g and k in o:
             got, want = g[k].cpu().numpy().reshape(-1), np.asarray(o[k]).reshape(-1)
             assert np.array_equal(got.view(np.uint32), want.astype(got.dtype).view(np.uint32)), k
+
+
+def test_single_layer_refuses_more_rows_than_the_spread_tiles_hold(ql):
+    """2048 rows of 500 cells have no tiling that leaves room for the codes."""
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(24, 500, 1, seed=1)["layers"][0]
+    with pytest.raises(ql.QLError, match="not supported"):
+        ql.lstm_layer_forward(ql.quantize_layer(w), torch.zeros(1, 2048, 24, device="cuda"))

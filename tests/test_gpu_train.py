@@ -139,3 +139,10 @@ def test_train_step_rejects_projection_layers(ql):
 def test_train_backward_xcd_rows(ql, orc, H, T, B):
     w, x, y = _case(24, H, 2, 40, T, B, seed=H + T + B)
     _compare(ql, orc, w, x, y, lr=0.5, quantize_output=True)
+
+
+def test_train_step_refuses_more_rows_than_the_backward_tiles_hold(ql):
+    """32 tiles of 16 cells times nine slices of 16 rows are more than the CUs."""
+    w, x, y = _case(24, 500, 1, 40, 2, 129, seed=3)
+    with pytest.raises(ql.QLError, match="not supported"):
+        ql.train_step(ql.train_params(w), torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.5)
