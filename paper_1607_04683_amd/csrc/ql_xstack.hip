@@ -469,6 +469,7 @@ __global__ __launch_bounds__(kXsThreads) void k_xstack(StackArgs a, XsTiling tl)
     
   };
   recover_x(0, wave0, fr0, fq0);
+  __syncthreads();  // every wave has read x_0 and its rows' params: step 0 puts x_1 in their place
 
   // the words of the poll for the codes of h (E2): word i of a thread is row
   // 4 i + tid / 128, word tid % 128 (a row has at most 128)

@@ -133,3 +133,23 @@ def test_stack_forward_still_takes_one_launch_only(ql):
     assert ql.stack_layers_per_launch(M, 2, 150) < 5
     with pytest.raises(ql.QLError, match="not supported"):
         ql.lstm_stack_forward(M.layers, ql.quantize_activations(x.reshape(300, 40)), 2, 150)
+
+
+@pytest.mark.parametrize("layers,n_in,H,T,B", [
+    (3, 512, 512, 2, 48),    # 32-cell tiles
+    (5, 320, 500, 3, 96),    # 64-cell tiles
+])
+def test_first_frame_is_read_before_the_second_replaces_it(ql, orc, layers, n_in, H, T, B):
+    """x_0 and x_1 share a buffer, and their values, zero points and recovery
+    factors are far apart here, so a wave that multiplied or recovered x_0 after
+    another had put x_1 there would change acc_x or the gates of frame 0."""
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(n_in, H, layers, states=24, seed=layers + B)
+    x = np.random.default_rng(B).standard_normal((T, B, n_in)).astype(np.float32)
+    x[0] = 5.0 + 1e-3 * x[0]
+    x[1] = -40.0 + 30.0 * x[1]
+    M, xd = ql.quantize_model(w), torch.from_numpy(x).cuda()
+    o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
+    for _ in range(4):
+        assert_model_taps(ql.acoustic_model_forward(M, xd, taps=True), o, None,
+                          names=("acc_x", "gates", "h_codes"))
