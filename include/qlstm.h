@@ -156,7 +156,8 @@ ql_status ql_dequantize(const ql_qmatrix *q, float *dst, void *stream);
 /* ---- quantized layer product (Fig. 1: R(Mult(Q(X), W')) + B) ---------------
  * X [m][cols] fp32 is quantized on the fly (per tensor or per row), multiplied
  * by W'^T and recovered: Y [m][rows] fp32 (+ bias[rows] when non-null).
- * acc [m][rows] (nullable) receives sum_k W'[n][k] x'[i][k]. */
+ * acc [m][rows] (nullable) receives sum_k W'[n][k] x'[i][k].  Y or acc may lie
+ * on X (an in-place product): X is then read before either is written. */
 size_t ql_quantized_matmul_workspace(int64_t m, int64_t rows, int64_t cols);
 ql_status ql_quantized_matmul(const ql_qmatrix *W, const float *X, int64_t m,
                               ql_act_gran gran, const float *bias, float *Y,

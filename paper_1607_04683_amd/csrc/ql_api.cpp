@@ -85,6 +85,12 @@ int enum_arg(const E &e) {
   return v;
 }
 
+// Whether [a, a + an) and [b, b + bn) share a byte (null: no buffer).
+bool share_bytes(const void *a, size_t an, const void *b, size_t bn) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + bn && y < x + an;
+}
+
 // True when a buffer of the initial states (per layer h [B][R], c [B][H])
 // shares a byte with a buffer of the final states: the kernels read the one
 // and write the other within a launch.
@@ -271,10 +277,15 @@ ql_status ql_quantized_matmul(const ql_qmatrix *W, const float *X, int64_t m, ql
   if (m < 0) return QL_ESHAPE;
   if (!ws || ws_bytes < ql_quantized_matmul_workspace(m, W->rows, W->cols)) return QL_EWORKSPACE;
   hipStream_t s = as_stream(stream);
-  bool done = false;
-  hipError_t es = launch_qmm_small(X, g == QL_ACT_PER_ROW, weight(*W), m, W->rows, W->cols, bias, Y, acc,
-                                   s, &done);
-  if (es != hipSuccess || done) return from_hip(es);
+  // in one launch every workgroup reads X while others store: only where no
+  // result lies on X (the launches below read X before they store anything)
+  const size_t xb = (size_t)(m * W->cols) * sizeof(float), yb = (size_t)(m * W->rows) * 4;
+  if (!share_bytes(X, xb, Y, yb) && !share_bytes(X, xb, acc, yb)) {
+    bool done = false;
+    const hipError_t e = launch_qmm_small(X, g == QL_ACT_PER_ROW, weight(*W), m, W->rows, W->cols, bias, Y,
+                                          acc, s, &done);
+    if (e != hipSuccess || done) return from_hip(e);
+  }
   Carve c(ws);
   ActBuf x = take_act(c, m, W->cols);
   void *qws = c.take<char>(set_quantize_ws(m, W->cols, 1));

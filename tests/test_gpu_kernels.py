@@ -4,6 +4,8 @@ Integer results (codes, zero points, accumulators, code sums) must be
 bit-exact; fp32 results that both sides compute with the same IEEE operations
 (recovery factors, recovered products, gate functions) are required bit-exact
 as well, which is stronger than the 1e-4 tolerance on float outputs."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -254,3 +256,31 @@ def test_softmax_few_rows(ql, orc, m, S):
     assert np.max(np.abs(post.sum(-1) - 1.0)) < 1e-5
     plain = ql.acoustic_model_forward(ql.quantize_model(w), torch.from_numpy(x).cuda())["post"]
     assert torch.equal(plain, g["post"])
+
+
+# Results that lie on X, wholly or in part: the sizes around the one-launch
+# product's (more than one workgroup of 64 rows of W').
+@pytest.mark.parametrize("m,rows,cols", [(16, 512, 512), (64, 128, 128), (64, 130, 128), (33, 200, 248),
+                                         (65, 128, 128)])
+@pytest.mark.parametrize("gran", [0, 1])
+@pytest.mark.parametrize("what,offset", [("Y", 0), ("Y", -1), ("acc", 64)])
+def test_qmatmul_on_its_input(ql, m, rows, cols, gran, what, offset):
+    rng = np.random.default_rng(m + rows)
+    W = ql.quantize(torch.from_numpy(rng.normal(0, 0.1, (rows, cols)).astype(np.float32)).cuda())
+    X = torch.from_numpy(rng.uniform(-1, 1, (m, cols)).astype(np.float32)).cuda()
+    want_y, want_acc = ql.quantized_matmul(W, X, gran, want_acc=True)
+    n, ny, at = m * cols, m * rows, 256
+    buf = torch.zeros(at + max(n, ny) + 256, device="cuda")
+    buf[at:at + n] = X.reshape(-1)
+    apart = torch.empty(ny, dtype=torch.int32, device="cuda")
+    on_x = buf.data_ptr() + 4 * (at + offset)
+    y, acc = (on_x, apart.data_ptr()) if what == "Y" else (apart.data_ptr(), on_x)
+    lib, cs = ql.load(), W.cstruct()
+    ws = torch.empty(lib.ql_quantized_matmul_workspace(m, rows, cols), dtype=torch.uint8, device="cuda")
+    assert lib.ql_quantized_matmul(ctypes.byref(cs), buf.data_ptr() + 4 * at, m, gran, None, y, acc,
+                                   ws.data_ptr(), ws.numel(), ql._stream()) == ql.QL_OK
+    torch.cuda.synchronize()
+    got = buf[at + offset:at + offset + ny]
+    y, acc = (got, apart) if what == "Y" else (apart.view(torch.float32), got.view(torch.int32))
+    assert torch.equal(y.view(torch.int32), want_y.reshape(-1).view(torch.int32))
+    assert torch.equal(acc, want_acc.reshape(-1))
