@@ -74,13 +74,16 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
   __shared__ __attribute__((aligned(16))) int8_t s_wr[WRL ? 16 : 1][kXvLds];
   __shared__ XvRow s_hp[2][NR], s_xp[2][NR], s_mp[NR];
   __shared__ float s_xb[2][NR][4 * kXvCells];  // W_x x + b, by parity
-  __shared__ int s_abort, s_role;
+  // expired waits, by the parity of the barrier that the writer has yet to pass:
+  // after a barrier only its own word is read, which nobody writes before the
+  // next one, so every wave leaves at the same barrier
+  __shared__ int s_abort[2], s_role;
 
   if (threadIdx.x == 0) {
     const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15);
     unsigned *slots = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
     s_role = -1;
-    s_abort = 0;
+    s_abort[0] = s_abort[1] = 0;
     if (xcc < a.nl * tl.ng) {
       const unsigned k = __hip_atomic_fetch_add(slots + xcc * 16, 1u, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
@@ -235,6 +238,7 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
       }
     }
   };
+  int turn = 0, stop = 0;  // parity of the next barrier (those of `take`); an expired wait
   // the words of x_t, once they carry its tag, to LDS
   auto land_x = [&](int t) __attribute__((always_inline)) {
     if (cin) {
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
                  ((uint32_t)(xz[r] >> 32) ^ tag) | ((uint32_t)(xq[r] >> 32) ^ tag);
         if (!__any(bad != 0)) break;
         if (wait_expired(flag, it)) {
-          s_abort = 1;
+          s_abort[turn] = 1;
           break;
         }
         issue_x(t);
@@ -290,7 +294,6 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
   // ---- waves 0-3: rows of n values (a row every n words), polled (tag > 0; else
   // from init, null: zeros), quantized, their codes and params in LDS; ends with
   // the workgroup's barrier
-  int stop = 0;
   auto take = [&](const uint64_t *words, const float *init, int n, uint32_t tag, int8_t *codes,
                   XvRow *params) __attribute__((always_inline)) {
     if (hside) {
@@ -327,7 +330,7 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
             }
           if (!__any(bad != 0)) break;
           if (wait_expired(flag, it)) {
-            s_abort = 1;
+            s_abort[turn] = 1;
             break;
           }
         }
@@ -363,7 +366,8 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
       }
     }
     __syncthreads();
-    stop |= __builtin_amdgcn_readfirstlane(s_abort);
+    stop |= __builtin_amdgcn_readfirstlane(s_abort[turn]);
+    turn ^= 1;
   };
   auto take_h = [&](int t) __attribute__((always_inline)) {
     take(hx + (int64_t)((t - 1) & 1) * rows * R, Ly.h0, R, (uint32_t)t, s_xh[t & 1][0], s_hp[t & 1]);

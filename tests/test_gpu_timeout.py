@@ -61,6 +61,17 @@ def test_layer_wavefront_times_out_and_recovers(ql, B):
     assert torch.equal(ql.acoustic_model_forward(M, x)["post"], ref)
 
 
+@pytest.mark.parametrize("B,proj", [(6, 0), (5, 24), (20, 24)])
+def test_few_row_wavefront_times_out_and_recovers(ql, B, proj):
+    """Four rows a group; with a projection in one launch of fours and in two
+    of eights."""
+    w, x = _model(ql, B, proj=proj, seed=B)
+    M = ql.quantize_model(w)
+    ref = ql.acoustic_model_forward(M, x)["post"]
+    _times_out(ql, lambda: ql.acoustic_model_forward(M, x))
+    assert torch.equal(ql.acoustic_model_forward(M, x)["post"], ref)
+
+
 @pytest.mark.parametrize("H,B,layout", [(64, 20, 1), (42, 20, 0), (64, 5, 0)])
 def test_projection_recurrence_times_out_and_recovers(ql, H, B, layout):
     """The XCD-local layout (batch 20) and the spread one (42 cells; batch 5)."""
