@@ -66,7 +66,9 @@ struct XbLay {
 template <int NG>
 __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int s_abort, s_role;
+  // expired waits, by step parity: the word of a step is read after its one
+  // barrier and written again only after the next, so every wave leaves there
+  __shared__ int s_abort[2], s_role;
   using L = XbLay<NG>;
   constexpr int NR = 4 * NG;
   constexpr int NA = NG == 1 ? 4 : NG == 2 ? 2 : 1;              // accumulators per row group
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
     const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15);
     unsigned *slots = reinterpret_cast<unsigned *>(static_cast<char *>(a.ws) + kHeaderBytes);
     s_role = -1;
-    s_abort = 0;
+    s_abort[0] = s_abort[1] = 0;
     if (xcc < kXbXcds) {
       const unsigned k = __hip_atomic_fetch_add(slots + xcc * 16, 1u, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
                 return src + (i & 7) * L::src + ((tid + kXbThreads * (i >> 3)) >> 2);
               },
               flag))
-        s_abort = 1;
+        s_abort[t & 1] = 1;
 #pragma unroll
       for (int r = 0; r < NQ; ++r)
 #pragma unroll
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kXbThreads) void k_xbptt(BpttArgs a, XbTiling tl) {
 #pragma unroll
     for (int r = 0; r < NQ; ++r) op.g[r] = opn.g[r], op.x[r] = opn.x[r];
     __syncthreads();
-    if (s_abort) return;
+    if (s_abort[t & 1]) return;
     if (t == 0) break;
 
     // ---- 3. this tile's part of W_h^T da_t, published for step t - 1
