@@ -153,14 +153,23 @@ __global__ __launch_bounds__(kXfThreads) void k_xrec_f32(F32RecArgs a, XfTiling 
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         h[g][c] = xs[(4 * g + (lane & 3)) * kXfLdx + kw + 16 * c + (lane >> 2)];
-    static_for<0, 64>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      if (k % 4 != 0 || k < kpw)  // (kpw is a multiple of 4: one test skips four)
+    auto four = [&](auto qc) __attribute__((always_inline)) {
+      static_for<4 * decltype(qc)::value, 4 * decltype(qc)::value + 4>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-          acc[g][k % NA] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[g][k / 16], w[k], acc[g][k % NA], 4,
-                                                              k % 16, 0);
-    });
+          acc[g][k % NA] =
+              __builtin_amdgcn_mfma_f32_4x4x1f32(h[g][k / 16], w[k], acc[g][k % NA], 4, k % 16, 0);
+      });
+    };
+    // (kpw is a multiple of 4: one test skips four.  Layers of over 480 cells have
+    // nothing to skip, and the tests would cost one row 7% of its step)
+    if (kpw == 64)
+      static_for<0, 16>(four);
+    else
+      static_for<0, 16>([&](auto qc) {
+        if (4 * decltype(qc)::value < kpw) four(qc);
+      });
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       // the results are read by ordinary instructions below: enough wait
