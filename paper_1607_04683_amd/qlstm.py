@@ -246,8 +246,14 @@ class QMatrix:
 
     @staticmethod
     def empty(rows: int, cols: int, nblocks: int, device) -> "QMatrix":
-        # (the quantizer writes the rows' padding too)
-        return QMatrix(torch.empty(rows, ld_for(cols), dtype=torch.int8, device=device), rows,
+        """Room for a matrix, its codes (and so their padding) zero."""
+        return QMatrix._around(torch.zeros(rows, ld_for(cols), dtype=torch.int8, device=device),
+                               cols, nblocks)
+
+    @staticmethod
+    def _around(codes: torch.Tensor, cols: int, nblocks: int) -> "QMatrix":
+        rows, device = codes.shape[0], codes.device
+        return QMatrix(codes, rows,
                        cols, nblocks, torch.empty(nblocks, dtype=torch.float64, device=device),
                        torch.empty(nblocks, dtype=torch.int32, device=device),
                        torch.empty(nblocks, dtype=torch.float32, device=device),
@@ -259,7 +265,9 @@ def quantize(W: torch.Tensor, nblocks: int = 1) -> QMatrix:
     W = W.contiguous()
     assert W.dtype == torch.float32 and W.dim() == 2
     rows, cols = W.shape
-    q = QMatrix.empty(rows, cols, nblocks, W.device)
+    # (the quantizer writes the rows' padding too)
+    q = QMatrix._around(torch.empty(rows, ld_for(cols), dtype=torch.int8, device=W.device), cols,
+                        nblocks)
     lib = load()
     nbytes = lib.ql_quantize_workspace(rows, cols, nblocks)
     ws = _ws(nbytes, W.device)

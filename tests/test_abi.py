@@ -47,6 +47,20 @@ def test_status_strings(ql):
         assert ql.status_str(s) and ql.status_str(s) != "unknown status"
 
 
+def test_empty_matrix_has_zero_codes(ql):
+    """A caller who fills codes[:, :cols] needs the padding to be zero.  Memory
+    that torch leaves uninitialized is filled with the type's largest value."""
+    import torch
+    before = torch.are_deterministic_algorithms_enabled()
+    torch.use_deterministic_algorithms(True)
+    try:
+        assert torch.empty(64, dtype=torch.int8).all()
+        q = ql.QMatrix.empty(3, 70, 1, "cpu")
+    finally:
+        torch.use_deterministic_algorithms(before)
+    assert q.codes.shape == (3, 128) and not q.codes.any()
+
+
 FAKE = 0x1000  # never dereferenced: each call below fails validation first
 
 
