@@ -425,6 +425,15 @@ int32_t ql_debug_recurrence_layout(const ql_lstm_layer *L, int64_t B);
  * -1 for an invalid layer, n < 1, T < 0 or B < 0.  The layers are read, never
  * written. */
 int32_t ql_debug_stack_layout(const ql_lstm_layer *layers, int32_t n, int64_t T, int64_t B);
+/* Test hook: which kernel the first persistent launch of ql_acoustic_model_forward
+ * over M's layers is for T frames of B utterances on the current device (M->Wy and
+ * M->by are not looked at) -- 0: one launch per layer; several layers a launch --
+ * 1: tiles spread over the chip; the whole chip with layers on XCDs of their own
+ * -- 2: one batch row; 3, 4: groups of up to four, eight rows; 5, 6: units of up
+ * to 16 rows in tiles of 32, 64 cells.  *launches (nullable): how many launches
+ * those layers take, each over a part of the batch (one per layer where the
+ * result is 0).  -1 for an invalid model, T < 0 or B < 0. */
+int32_t ql_debug_model_layout(const ql_model *M, int64_t T, int64_t B, int32_t *launches);
 /* Elementwise gate functions on device arrays (fn 0 = e^x, 1 = sigmoid,
  * 2 = tanh, 3 = the reciprocal 1 / d that sigmoid applies to d = 1 + e^-x,
  * defined for d in [1, 2^126) and equal there to IEEE division) -- the exact

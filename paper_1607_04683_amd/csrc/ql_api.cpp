@@ -457,22 +457,32 @@ PStackLayer pstack_layer(const ql_lstm_layer &L, const ActRows &xin, const ActBu
 // Layers that all have a projection, at two or more batch rows, run as row
 // groups of the whole chip where their exchange fits the space of W_x x + b,
 // which that layout does not form.  *done false: one layer per launch.
+size_t proj_word_bytes(int64_t MB, int64_t maxH) { return (size_t)(MB * 4 * maxH) * sizeof(float); }
+PStackArgs proj_rows_args(const ql_model &M, const ActRows &xin, const ActBuf &last, int64_t T, int64_t B,
+                          void *ws, const ql_model_taps *taps, const ql_lstm_state *s0,
+                          const ql_lstm_state *s1) {
+  PStackArgs a{};
+  if (B < 2 || M.nlayers < 2 || M.nlayers > kMaxStack) return a;
+  a.T = T;
+  a.B = B;
+  a.ws = ws;
+  for (int l = 0; l < M.nlayers; ++l) {
+    if (M.layers[l].proj <= 0) return a;
+    const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l] : nullptr;
+    const bool top = l == M.nlayers - 1;
+    a.L[l] = pstack_layer(M.layers[l], l == 0 ? xin : ActRows{}, top ? last : ActBuf{}, lt, s0, s1, l);
+  }
+  a.nl = M.nlayers;  // (0: not such a model)
+  return a;
+}
 ql_status run_proj_rows(const ql_model &M, const ActRows &xin, const ActBuf &last, int64_t T, int64_t B,
                         void *ws, void *words, size_t word_bytes, const ql_model_taps *taps,
                         const ql_lstm_state *s0, const ql_lstm_state *s1, hipStream_t s, bool *done) {
   *done = false;
-  if (B < 2 || M.nlayers < 2 || M.nlayers > kMaxStack) return QL_OK;
-  PStackArgs a{};
-  a.nl = M.nlayers;
-  a.T = T;
-  a.B = B;
-  a.ws = ws;
+  const PStackArgs a = proj_rows_args(M, xin, last, T, B, ws, taps, s0, s1);
+  if (a.nl == 0) return QL_OK;
   bool tp = false;
-  for (int l = 0; l < M.nlayers; ++l) {
-    if (M.layers[l].proj <= 0) return QL_OK;
-    const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l] : nullptr;
-    const bool top = l == M.nlayers - 1;
-    a.L[l] = pstack_layer(M.layers[l], l == 0 ? xin : ActRows{}, top ? last : ActBuf{}, lt, s0, s1, l);
+  for (int l = 0; l < a.nl; ++l) {
     const PStackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.acc_r || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
@@ -644,8 +654,8 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   if (!stack && !pst) {
     ActBuf last = mw.out[0];
     last.ld = round_up(layer_width(M->layers[M->nlayers - 1]), 64);
-    st = run_proj_rows(*M, cur, last, T, B, mw.rec, mw.gx, (size_t)(MB * 4 * maxH) * sizeof(float), taps,
-                       s0, s1, s, &whole);
+    st = run_proj_rows(*M, cur, last, T, B, mw.rec, mw.gx, proj_word_bytes(MB, maxH), taps, s0, s1,
+                       s, &whole);
     if (st != QL_OK) return st;
     if (whole) cur = last.rows();
   }
@@ -1076,6 +1086,64 @@ ql_status ql_debug_set_wait_bound(int32_t polls) {
   return set_wait_bound(polls) == hipSuccess ? QL_OK : QL_EHIP;
 }
 
+int32_t ql_debug_model_layout(const ql_model *M, int64_t T, int64_t B, int32_t *launches) {
+  if (!M || !M->layers || M->nlayers < 1 || T < 0 || B < 0) return -1;
+  int64_t maxH = 0;
+  for (int l = 0; l < M->nlayers; ++l) {
+    const ql_lstm_layer &L = M->layers[l];
+    if (check_layer(&L) != QL_OK || (l > 0 && L.in != layer_width(M->layers[l - 1]))) return -1;
+    maxH = std::max(maxH, L.hidden);
+  }
+  // (the choices of model_forward, on shapes alone)
+  int32_t unused;
+  int32_t &nlaunch = launches ? *launches : unused;
+  nlaunch = M->nlayers;
+  const int n_all = M->nlayers;
+  if (T == 0 || B == 0) return kPathLayers;
+  ActRows xin{};
+  xin.ld = round_up(M->layers[0].in, 64);
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return kPathLayers;
+  }
+  const bool stack = stackable(*M), pst = !stack && pstack_shapes(M->layers, n_all, B);
+  if (!stack && !pst) {
+    int k = 0;
+    const PStackArgs a = proj_rows_args(*M, xin, ActBuf{}, T, B, nullptr, nullptr, nullptr, nullptr);
+    const int nr = a.nl ? xrows_applies(a, proj_word_bytes(T * B, maxH), cus, &k) : 0;
+    if (nr) nlaunch = k;
+    return nr == 0 ? kPathLayers : nr == 4 ? kPathXrows4 : kPathXrows8;
+  }
+  const int per = stack ? stack_layers_routed(n_all, T, B, maxH, M->layers[0].in, M->layers[1].in)
+                        : pstack_per_launch(M->layers, n_all, T, B);
+  const int groups = (n_all + per - 1) / per, n = (n_all + groups - 1) / groups;
+  if (n < 2) return kPathLayers;
+  nlaunch = 1;
+  auto out = [&](int l) {
+    ActBuf b{};
+    b.ld = round_up(layer_width(M->layers[l]), 64);
+    return b;
+  };
+  if (pst) {
+    PStackArgs a{};
+    int64_t hs[kMaxStack], ps[kMaxStack];
+    a.nl = n, a.T = T, a.B = 1;
+    for (int l = 0; l < n; ++l) {
+      a.L[l] = pstack_layer(M->layers[l], l == 0 ? xin : ActRows{}, out(l), nullptr, nullptr, nullptr, l);
+      hs[l] = M->layers[l].hidden, ps[l] = M->layers[l].proj;
+    }
+    return xrow_applies(a, pstack_ws(hs, ps, n, T), cus) ? kPathXrow : kPathSpread;
+  }
+  StackArgs a{};
+  a.nl = n, a.T = T, a.B = B, a.H = maxH;
+  for (int l = 0; l < n; ++l)
+    a.L[l] = stack_layer(M->layers[l], l == 0 ? xin : ActRows{}, out(l), nullptr, nullptr, nullptr, l);
+  const int path = stack_chip_path(a, stack_ws(n, T, B, maxH), &nlaunch);
+  if (path == kPathLayers) nlaunch = 1;
+  return path == kPathLayers ? kPathSpread : path;
+}
 int32_t ql_debug_recurrence_layout(const ql_lstm_layer *L, int64_t B) {
   if (check_layer(L) != QL_OK || B < 0) return -1;
   ActBuf out{};

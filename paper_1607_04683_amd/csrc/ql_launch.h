@@ -231,6 +231,17 @@ hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_m
 // 1 when launch_stack would run a in that layout at batch 16 to 64 on the
 // current device, else 0.
 int stack_layout(const StackArgs &a);
+// Which of the layouts launch_stack_chip would run a in with ws_bytes of scratch,
+// and over how many launches (the values ql_debug_model_layout reports).
+enum { kPathLayers = 0, kPathSpread, kPathXrow, kPathXrows4, kPathXrows8, kPathXstack32, kPathXstack64 };
+bool xrow_applies(const StackArgs &a, size_t ws_bytes, int cus);
+bool xrow_applies(const PStackArgs &a, size_t ws_bytes, int cus);
+// Rows per group the few-row layout is built for, 4 or 8; 0: it does not take a.
+int xrows_applies(const StackArgs &a, size_t ws_bytes, int cus, int *launches);
+int xrows_applies(const PStackArgs &a, size_t word_bytes, int cus, int *launches);
+// Launches of the 16-row units, and their cells per tile; 0: they do not take a.
+int xstack_launches(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, int *cells);
+int stack_chip_path(const StackArgs &a, size_t ws_bytes, int *launches);
 // How many layers of such a stack fit one launch (1: none, use the one-layer path).
 int stack_layers_per_launch(int n, int64_t T, int64_t B, int64_t H, int64_t in0, int64_t in1);
 // Whether all of a's layers and rows go into one launch (what

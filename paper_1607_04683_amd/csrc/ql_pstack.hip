@@ -2,7 +2,8 @@
 // (Section 4: 5 x 500 cells with P = 100 .. 400 projection units) at one batch
 // row, all in one persistent launch run as a wavefront: while layer l works on
 // frame t, layer l-1 is already on a later frame.  This is the layout of a
-// partition of the chip; the whole chip runs ql_xrow.hip.
+// partition of the chip; the whole chip runs ql_xrow.hip, but for a few shapes with
+// one or two projection units, whose words there are more than the scratch holds.
 //
 // A tile owns u cells of one layer (the 4u gate rows of W_x' and W_h', resident
 // in LDS) and v rows of the layer's projection W_r' (also resident).  Per
@@ -390,7 +391,8 @@ hipError_t launch_pstack(const PStackArgs &a, hipStream_t s, bool *unsupported) 
     tp = tp || L.acc_x || L.acc_h || L.acc_r || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
   {
-    // the whole chip: one XCD per layer
+    // the whole chip: one XCD per layer (declined where P is 1 or 2 and its words,
+    // up to four more a layer, do not fit the scratch of this kernel)
     int64_t hs[kMaxStack], ps[kMaxStack];
     for (int l = 0; l < a.nl; ++l) hs[l] = a.L[l].H, ps[l] = a.L[l].P;
     bool done = false;

@@ -930,34 +930,59 @@ int stack_layout(const StackArgs &a) {
              : 0;
 }
 
+static hipError_t chip_props(int *cus, int *lds_max) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  return e;
+}
+
+// The batches taken by the whole-chip layouts: those of a launch per layer or of
+// k_stack.
+static bool chip_takes_batch(const StackArgs &a, int cus, int lds_max) {
+  if (a.B <= 64) return true;
+  RecurrentArgs r{};
+  r.T = a.T, r.B = a.B, r.H = r.R = a.H;
+  return recurrent_fits(r, cus, lds_max) ||
+         stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.nl > 1 ? a.L[1].in : a.H) >= 2;
+}
+
 hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s, bool *done) {
   *done = false;
   if (a.T == 0 || a.B == 0 || a.nl < 1 || a.nl > kMaxStack || a.H > 512) return hipSuccess;
-  int dev = 0, cus = 0, lds_max = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess)
-    e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  int cus = 0, lds_max = 0;
+  hipError_t e = chip_props(&cus, &lds_max);
   if (e != hipSuccess) return e;
   bool tp = false;  // any tap or final state asked for
   for (int l = 0; l < a.nl; ++l) {
     const StackLayer &L = a.L[l];
     tp = tp || L.acc_x || L.acc_h || L.tap_gates || L.tap_c || L.tap_m || L.hT || L.cT;
   }
-  // the batches taken are those of a launch per layer or of k_stack
-  if (a.B > 64) {
-    RecurrentArgs r{};
-    r.T = a.T, r.B = a.B, r.H = r.R = a.H;
-    if (!recurrent_fits(r, cus, lds_max) &&
-        stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.nl > 1 ? a.L[1].in : a.H) < 2)
-      return hipSuccess;
-  }
+  if (!chip_takes_batch(a, cus, lds_max)) return hipSuccess;
   // one batch row, or up to four per group, with an XCD per layer; more as
   // units of 16
   if (a.B == 1) return launch_xrow(a, ws_bytes, cus, tp, s, done);
   e = launch_xrows(a, ws_bytes, cus, tp, s, done);
   if (e != hipSuccess || *done) return e;
   return launch_xstack(a, ws_bytes, cus, lds_max, tp, s, done);
+}
+
+int stack_chip_path(const StackArgs &a, size_t ws_bytes, int *launches) {
+  *launches = 1;
+  int cus = 0, lds_max = 0;
+  if (a.T == 0 || a.B == 0 || a.nl < 1 || a.nl > kMaxStack || a.H > 512) return kPathLayers;
+  if (chip_props(&cus, &lds_max) != hipSuccess) {
+    (void)hipGetLastError();
+    return kPathLayers;
+  }
+  if (!chip_takes_batch(a, cus, lds_max)) return kPathLayers;
+  if (a.B == 1) return xrow_applies(a, ws_bytes, cus) ? kPathXrow : kPathLayers;
+  if (xrows_applies(a, ws_bytes, cus, launches)) return kPathXrows4;
+  int cells = 0;
+  *launches = xstack_launches(a, ws_bytes, cus, lds_max, &cells);
+  return *launches == 0 ? kPathLayers : cells == 32 ? kPathXstack32 : kPathXstack64;
 }
 
 hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {

@@ -407,27 +407,35 @@ __global__ __launch_bounds__(kXwThreads) void k_xrow(Args a) {
 }
 
 // ------------------------------------------------------------------ host side
+// Whether the layout takes a; its exchange words.
 template <class Args>
-static hipError_t launch_xrow_any(const Args &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
-                                  bool *done) {
+static bool plan_xrow(const Args &a, size_t ws_bytes, int cus, int64_t *words_out) {
   constexpr bool PROJ = std::is_same<Args, PStackArgs>::value;
-  *done = false;
   if (cus != kXwXcds * kXwSlots || a.nl < 1 || a.nl > kXwXcds || a.T < 1 || a.T >= (1 << 30))
-    return hipSuccess;
+    return false;
   int64_t words = 0;
   for (int l = 0; l < a.nl; ++l) {
     const auto &L = a.L[l];
     const int64_t H = xrow_cells(a, l), R = xrow_width(a, l);
-    if (H < 1 || H > kXwMaxW || R < 1 || R > kXwMaxW || L.in < 1 || L.in > kXwMaxW) return hipSuccess;
-    if (l > 0 && L.in != xrow_width(a, l - 1)) return hipSuccess;
-    if (L.Wx.ld < round_up(L.in, 64) || L.Wh.ld < round_up(R, 64)) return hipSuccess;
+    if (H < 1 || H > kXwMaxW || R < 1 || R > kXwMaxW || L.in < 1 || L.in > kXwMaxW) return false;
+    if (l > 0 && L.in != xrow_width(a, l - 1)) return false;
+    if (L.Wx.ld < round_up(L.in, 64) || L.Wh.ld < round_up(R, 64)) return false;
     if constexpr (PROJ)
-      if (L.Wr.ld < round_up(H, 64)) return hipSuccess;
-    if (L.out.ld < R || L.out.ld % 4) return hipSuccess;
+      if (L.Wr.ld < round_up(H, 64)) return false;
+    if (L.out.ld < R || L.out.ld % 4) return false;
     words += xrow_words(H, R, PROJ, a.T);
   }
-  if (a.L[0].xin.ld % 8 || a.L[0].xin.ld < a.L[0].in) return hipSuccess;
-  if (kHeaderBytes + kXwSlotBytes + (size_t)words * 8 > ws_bytes) return hipSuccess;
+  if (a.L[0].xin.ld % 8 || a.L[0].xin.ld < a.L[0].in) return false;
+  *words_out = words;
+  return kHeaderBytes + kXwSlotBytes + (size_t)words * 8 <= ws_bytes;
+}
+
+template <class Args>
+static hipError_t launch_xrow_any(const Args &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
+                                  bool *done) {
+  *done = false;
+  int64_t words = 0;
+  if (!plan_xrow(a, ws_bytes, cus, &words)) return hipSuccess;
   auto kern = taps ? k_xrow<Args, true> : k_xrow<Args, false>;
   // more than half of a CU's LDS, so that a CU holds one workgroup
   const size_t lds = 84 * 1024;
@@ -457,6 +465,15 @@ hipError_t launch_xrow(const StackArgs &a, size_t ws_bytes, int cus, bool taps, 
 hipError_t launch_xrow(const PStackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,
                        bool *done) {
   return launch_xrow_any(a, ws_bytes, cus, taps, s, done);
+}
+
+bool xrow_applies(const StackArgs &a, size_t ws_bytes, int cus) {
+  int64_t words;
+  return a.B == 1 && plan_xrow(a, ws_bytes, cus, &words);
+}
+bool xrow_applies(const PStackArgs &a, size_t ws_bytes, int cus) {
+  int64_t words;
+  return plan_xrow(a, ws_bytes, cus, &words);
 }
 
 hipError_t set_wait_bound_xrow(int polls) { return set_wait_bound_here(polls); }

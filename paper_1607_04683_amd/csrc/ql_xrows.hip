@@ -512,25 +512,31 @@ __global__ __launch_bounds__(kXvThreads) void k_xrows(Args a, XvTiling tl) {
 }
 
 // ------------------------------------------------------------------ host side
+// How the layout takes a: rows per group it is built for (4 or 8; 0: it does
+// not take a), batch rows and exchange words of a launch.
+struct XvPlan {
+  XvTiling tl;
+  int nr;
+  int64_t launches, chunk, nwords;
+};
 template <class Args>
-static hipError_t launch_xrows_any(const Args &a, void *words, size_t word_bytes, int cus, bool taps,
-                                   hipStream_t s, bool *done) {
+static XvPlan plan_xrows(const Args &a, size_t word_bytes, int cus) {
   constexpr bool PROJ = std::is_same<Args, PStackArgs>::value;
-  *done = false;
+  XvPlan p{};
   if (cus != kXvXcds * kXvSlots || a.nl < 1 || a.nl > kXvXcds || a.T < 1 || a.T >= (1 << 30) || a.B < 1)
-    return hipSuccess;
+    return p;
   const int groups = kXvXcds / a.nl;
   for (int l = 0; l < a.nl; ++l) {
     const auto &L = a.L[l];
     const int64_t H = xv_cells(a, l), R = xv_width(a, l);
-    if (H < 1 || H > kXvMaxW || R < 1 || R > kXvMaxW || L.in < 1 || L.in > kXvMaxW) return hipSuccess;
-    if (l > 0 && L.in != xv_width(a, l - 1)) return hipSuccess;
-    if (L.Wx.ld < round_up(L.in, 64) || L.Wh.ld < round_up(R, 64)) return hipSuccess;
+    if (H < 1 || H > kXvMaxW || R < 1 || R > kXvMaxW || L.in < 1 || L.in > kXvMaxW) return p;
+    if (l > 0 && L.in != xv_width(a, l - 1)) return p;
+    if (L.Wx.ld < round_up(L.in, 64) || L.Wh.ld < round_up(R, 64)) return p;
     if constexpr (PROJ)
-      if (L.Wr.ld < round_up(H, 64)) return hipSuccess;
-    if (L.out.codes && (L.out.ld < R || L.out.ld % 4)) return hipSuccess;
+      if (L.Wr.ld < round_up(H, 64)) return p;
+    if (L.out.codes && (L.out.ld < R || L.out.ld % 4)) return p;
   }
-  if (a.L[0].xin.ld % 8 || a.L[0].xin.ld < a.L[0].in) return hipSuccess;
+  if (a.L[0].xin.ld % 8 || a.L[0].xin.ld < a.L[0].in) return p;
   // Groups of up to four rows while the chip has them, with a projection then of
   // up to eight, over launches of equal size, where that is the faster layout.
   // Through 5 x 500 cells, us a frame (100 frames, start-up included): without a
@@ -539,19 +545,30 @@ static hipError_t launch_xrows_any(const Args &a, void *words, size_t word_bytes
   // launch in eights, against 39-43 with one launch per layer (31-35 for 4
   // layers), about 8 a layer: as many launches as layers still pay.
   const int64_t most = (int64_t)groups * (PROJ ? 8 : 4);
-  const int64_t launches = (a.B + most - 1) / most, chunk = (a.B + launches - 1) / launches;
-  if (launches > (PROJ ? a.nl : 1)) return hipSuccess;
-  XvTiling tl{};
-  const int nr = chunk <= 4 * groups ? 4 : 8;
-  const int ng = (int)((chunk + nr - 1) / nr);
-  tl.rows = (int)((chunk + ng - 1) / ng);
-  int64_t n = 0;
-  for (int l = 0; l < a.nl; ++l) n += ng * xv_words(xv_cells(a, l), xv_width(a, l), PROJ, a.T, tl.rows);
-  if ((size_t)n * 8 > word_bytes) return hipSuccess;
+  p.launches = (a.B + most - 1) / most;
+  p.chunk = (a.B + p.launches - 1) / p.launches;
+  if (p.launches > (PROJ ? a.nl : 1)) return p;
+  const int nr = p.chunk <= 4 * groups ? 4 : 8;
+  const int ng = (int)((p.chunk + nr - 1) / nr);
+  p.tl.rows = (int)((p.chunk + ng - 1) / ng);
+  for (int l = 0; l < a.nl; ++l)
+    p.nwords += ng * xv_words(xv_cells(a, l), xv_width(a, l), PROJ, a.T, p.tl.rows);
+  if ((size_t)p.nwords * 8 <= word_bytes) p.nr = nr;
+  return p;
+}
+
+template <class Args>
+static hipError_t launch_xrows_any(const Args &a, void *words, size_t word_bytes, int cus, bool taps,
+                                   hipStream_t s, bool *done) {
+  constexpr bool PROJ = std::is_same<Args, PStackArgs>::value;
+  *done = false;
+  const XvPlan p = plan_xrows(a, word_bytes, cus);
+  if (!p.nr) return hipSuccess;
+  XvTiling tl = p.tl;
   tl.words = static_cast<uint64_t *>(words);
   auto kern = taps ? k_xrows<Args, 4, true> : k_xrows<Args, 4, false>;
   if constexpr (PROJ)
-    if (nr == 8) kern = taps ? k_xrows<Args, 8, true> : k_xrows<Args, 8, false>;
+    if (p.nr == 8) kern = taps ? k_xrows<Args, 8, true> : k_xrows<Args, 8, false>;
   // with the static part more than half of a CU's LDS, so that a CU holds one workgroup
   const size_t lds = 84 * 1024;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -561,11 +578,11 @@ static hipError_t launch_xrows_any(const Args &a, void *words, size_t word_bytes
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kXvThreads, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipSuccess;
-  for (int64_t r0 = 0; r0 < a.B; r0 += chunk) {
+  for (int64_t r0 = 0; r0 < a.B; r0 += p.chunk) {
     tl.r0 = r0;
-    tl.r1 = std::min(a.B, r0 + chunk);
+    tl.r1 = std::min(a.B, r0 + p.chunk);
     tl.ng = (int)((tl.r1 - r0 + tl.rows - 1) / tl.rows);
-    e = clear_exchange2(a.ws, kXvSlotBytes / 8, tl.words, n, s);
+    e = clear_exchange2(a.ws, kXvSlotBytes / 8, tl.words, p.nwords, s);
     if (e != hipSuccess) return e;
     Args args = a;
     XvTiling t = tl;
@@ -592,6 +609,18 @@ hipError_t launch_xrows(const StackArgs &a, size_t ws_bytes, int cus, bool taps,
 hipError_t launch_xrows(const PStackArgs &a, void *words, size_t word_bytes, int cus, bool taps,
                         hipStream_t s, bool *done) {
   return launch_xrows_any(a, words, word_bytes, cus, taps, s, done);
+}
+
+int xrows_applies(const StackArgs &a, size_t ws_bytes, int cus, int *launches) {
+  const size_t head = kHeaderBytes + kXvSlotBytes;
+  const XvPlan p = plan_xrows(a, ws_bytes < head ? 0 : ws_bytes - head, cus);
+  *launches = (int)p.launches;
+  return p.nr;
+}
+int xrows_applies(const PStackArgs &a, size_t word_bytes, int cus, int *launches) {
+  const XvPlan p = plan_xrows(a, word_bytes, cus);
+  *launches = (int)p.launches;
+  return p.nr;
 }
 
 hipError_t set_wait_bound_xrows(int polls) { return set_wait_bound_here(polls); }

@@ -761,6 +761,15 @@ bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max) {
   return plan_xstack(a, ws_bytes, cus, lds_max, 0, &tl);
 }
 
+int xstack_launches(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, int *cells) {
+  int n = 0;
+  XsTiling tl{};
+  for (int64_t r0 = 0; r0 < a.B; r0 = tl.r1, ++n)
+    if (!plan_xstack(a, ws_bytes, cus, lds_max, r0, &tl)) return 0;
+  *cells = 32 * tl.cb;
+  return n;
+}
+
 hipError_t launch_xstack(const StackArgs &a, size_t ws_bytes, int cus, int lds_max, bool taps,
                          hipStream_t s, bool *done) {
   *done = false;

@@ -37,6 +37,7 @@ EXPORTS = [
     "ql_acoustic_model_forward_frames", "ql_acoustic_model_forward_stream",
     "ql_acoustic_model_forward_stream_noalloc", "ql_train_step_workspace", "ql_train_step",
     "ql_debug_set_wait_bound", "ql_debug_recurrence_layout", "ql_debug_stack_layout",
+    "ql_debug_model_layout",
 ]
 
 
@@ -145,6 +146,8 @@ def load(path: str = LIB_PATH):
     L.ql_debug_recurrence_layout.restype = i32
     L.ql_debug_stack_layout.argtypes = [C.POINTER(CLayer), i32, i64, i64]
     L.ql_debug_stack_layout.restype = i32
+    L.ql_debug_model_layout.argtypes = [C.POINTER(CModel), i64, i64, C.POINTER(i32)]
+    L.ql_debug_model_layout.restype = i32
     L.ql_f32_matmul.argtypes = [vp, i64, i64, vp, i64, vp, vp, vp]
     L.ql_quantize_activations.argtypes = [vp, i64, i64, C.POINTER(CQAct), vp]
     L.ql_lstm_stack_workspace.argtypes = [C.POINTER(CLayer), i32, i64, i64]
@@ -832,3 +835,18 @@ def train_step(P: dict, feats: torch.Tensor, targets: torch.Tensor, lr: float,
     if check:
         _check(lib.ql_workspace_status(_ptr(ws), _stream()), "ql_train_step")
     return loss, grads
+
+
+MODEL_LAYOUTS = ("layers", "spread", "xrow", "xrows4", "xrows8", "xstack32", "xstack64")
+
+
+def model_layout(M: Model, T: int, B: int) -> tuple[str, int]:
+    """Which kernel the first persistent launch of acoustic_model_forward is for
+    T frames of B utterances (a name of MODEL_LAYOUTS), and over how many
+    launches those layers run."""
+    n = C.c_int32()
+    cm, _keep = M.cstruct()
+    k = load().ql_debug_model_layout(C.byref(cm), T, B, C.byref(n))
+    if k < 0:
+        raise ValueError("no layout: invalid model, T or B")
+    return MODEL_LAYOUTS[k], n.value

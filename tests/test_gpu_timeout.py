@@ -4,10 +4,10 @@ call whose workgroups must wait for each other gives up: the first wait that
 is not met at once raises the workspace flag, every workgroup leaves at its
 next wait (so the launch drains and the kernel ends normally), and the call
 reports QL_ETIMEOUT.  The next call with the default bound gives the same
-results, bit for bit, as a call made before.  Covers each persistent kernel:
-the batched and the one-row layer wavefronts, the one-layer recurrence with a
-projection (XCD-local and spread layouts), the fp32 recurrence, the training step's backward recurrence and
-the allocation-free entry point."""
+results, bit for bit, as a call made before.  Covers the layer wavefronts of one,
+a few and many rows, the one-layer recurrence with a projection (XCD-local and
+spread layouts), the fp32 recurrence, the training step's backward recurrence
+and the allocation-free entry point."""
 import numpy as np
 import pytest
 import torch
@@ -49,24 +49,29 @@ def _model(ql, B, layers=3, H=48, proj=0, seed=1):
     return w, x
 
 
-@pytest.mark.parametrize("B", [32, 1])
-def test_layer_wavefront_times_out_and_recovers(ql, B):
-    """B = 32: batched tiles (counters, quantizing workgroups); B = 1: one-row
-    tiles (tagged words)."""
-    w, x = _model(ql, B)
+@pytest.mark.parametrize("B,proj,layout", [(32, 0, "xstack32"), (90, 0, "xstack64"), (1, 0, "xrow"),
+                                           (1, 24, "xrow")])
+def test_layer_wavefront_times_out_and_recovers(ql, B, proj, layout):
+    """Units of 16 rows in tiles of 32 and 64 cells; one row, without and with a
+    projection."""
+    w, x = _model(ql, B, proj=proj)
     M = ql.quantize_model(w)
-    assert ql.stack_layers_per_launch(M, x.shape[0], B) >= 2
+    assert ql.model_layout(M, x.shape[0], B)[0] == layout
+    if B != 90:
+        assert ql.stack_layers_per_launch(M, x.shape[0], B) >= 2
     ref = ql.acoustic_model_forward(M, x)["post"]
     _times_out(ql, lambda: ql.acoustic_model_forward(M, x))
     assert torch.equal(ql.acoustic_model_forward(M, x)["post"], ref)
 
 
-@pytest.mark.parametrize("B,proj", [(6, 0), (5, 24), (20, 24)])
-def test_few_row_wavefront_times_out_and_recovers(ql, B, proj):
+@pytest.mark.parametrize("B,proj,layout", [(6, 0, ("xrows4", 1)), (5, 24, ("xrows4", 1)),
+                                           (20, 24, ("xrows8", 2))])
+def test_few_row_wavefront_times_out_and_recovers(ql, B, proj, layout):
     """Four rows a group; with a projection in one launch of fours and in two
     of eights."""
     w, x = _model(ql, B, proj=proj, seed=B)
     M = ql.quantize_model(w)
+    assert ql.model_layout(M, x.shape[0], B) == layout
     ref = ql.acoustic_model_forward(M, x)["post"]
     _times_out(ql, lambda: ql.acoustic_model_forward(M, x))
     assert torch.equal(ql.acoustic_model_forward(M, x)["post"], ref)

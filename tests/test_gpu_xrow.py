@@ -34,13 +34,15 @@ def ql():
     (8, 40, 100, 17, 6),
     (2, 512, 512, 512, 3),
     (5, 320, 500, 200, 20),
-    (3, 12, 40, 1, 4),       # one output: its frame words do not fit, the other kernel runs
+    (3, 12, 40, 1, 4),       # one output
+    (3, 12, 30, 1, 1),       # its words are two more a layer than k_pstack's scratch, which runs
 ])
 def test_one_row_stack_equals_oracle(ql, orc, layers, n_in, H, P, T):
     from paper_1607_04683_amd.workloads import random_model
     w = random_model(n_in, H, layers, proj=P, states=24, seed=layers * 1000 + H + P)
     x = np.random.default_rng(H + T).standard_normal((T, 1, n_in)).astype(np.float32)
     M = ql.quantize_model(w)
+    assert ql.model_layout(M, T, 1) == ("spread" if (H, P, T) == (30, 1, 1) else "xrow", 1)
     g = ql.acoustic_model_forward(M, torch.from_numpy(x).cuda(), taps=True)
     o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
     assert_model_taps(g, o, None, names=ql.TAP_NAMES)

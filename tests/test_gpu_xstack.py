@@ -26,8 +26,10 @@ def ql():
 
 # layers, n_in, H, T, B
 CASES = [
-    (2, 40, 48, 9, 16),      # the smallest batch: 8 rows per group (one 16-row MFMA tile)
-    (3, 24, 100, 6, 33),     # 17 + 16 rows; 100 cells: tiles 4..15 of a group hold none
+    (2, 40, 48, 9, 16),      # (two layers: four groups of four rows of the few-row layout)
+    (3, 40, 48, 9, 16),      # the smallest batch: one full 16-row MFMA tile
+    (2, 40, 48, 9, 17),      # two groups, of 9 and 8 rows
+    (3, 24, 100, 6, 33),     # three groups of 11 rows; 100 cells: tiles 4..15 of a group hold none
     (8, 40, 64, 5, 21),      # the most layers of one launch; 11 + 10 rows
     (2, 512, 512, 4, 64),    # the widest input and cell count at full batch
     (3, 320, 500, 4, 64),    # the 5 x 500 model's widths
@@ -45,6 +47,8 @@ def test_xcd_stack_equals_oracle(ql, orc, layers, n_in, H, T, B):
     M = ql.quantize_model(w)
     assert ql.stack_layers_per_launch(M, T, B) == layers
     assert ql.stack_layout(M, T, B) == 1
+    kernel = ql.model_layout(M, T, B)[0]
+    assert kernel == "xrows4" if (layers, B) == (2, 16) else kernel.startswith("xstack")
     g = ql.acoustic_model_forward(M, torch.from_numpy(x).cuda(), taps=True)
     o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
     assert_model_taps(g, o, None, names=ql.TAP_NAMES)
@@ -81,35 +85,39 @@ def test_xcd_stack_repeats_bit_for_bit(ql):
 
 # Row groups of up to 16 rows: 16 of them share the chip with 32-cell tiles, 32
 # with 64-cell tiles, several launches beyond.  Batches at the edges of these.
+# The last columns: the kernel that runs, and over how many launches.
 GROUP_CASES = [
-    (2, 40, 48, 6, 2),       # the smallest batch
-    (5, 40, 36, 5, 15),      # one group per layer, one row short
-    (5, 40, 36, 2, 48),      # the most rows of 5 layers in 32-cell tiles
-    (5, 40, 48, 4, 49),      # one row more: 64-cell tiles, 4 groups of 13
-    (8, 24, 64, 5, 33),      # 2 groups of 16 at most: 64-cell tiles, 3 of 11
-    (3, 24, 100, 4, 65),     # 5 groups of 13 rows; tiles without cells
-    (5, 40, 500, 3, 97),     # one row more than a launch holds: 49 + 48
-    (4, 512, 512, 2, 128),   # a full launch at the widest
-    (3, 320, 260, 3, 190),   # two launches of 6 groups
-    (5, 24, 16, 3, 150),     # narrow cells: the scratch holds fewer groups
-    (9, 24, 32, 3, 20),      # more layers than one launch holds: 5 + 4
-    (3, 40, 130, 1, 60),     # one frame in 64-cell tiles
+    (2, 40, 48, 6, 2, "xrows4", 1),      # (two rows: the few-row layout)
+    (5, 40, 36, 3, 5, "xstack32", 1),    # the smallest batch of five layers
+    (5, 40, 36, 5, 15, "xstack32", 1),   # one group per layer, one row short
+    (5, 40, 36, 2, 48, "xstack32", 1),   # the most rows of 5 layers in 32-cell tiles
+    (5, 40, 48, 4, 49, "xstack64", 1),   # one row more: 64-cell tiles, 4 groups of 13
+    (8, 24, 64, 5, 33, "xstack64", 1),   # 2 groups of 16 at most: 64-cell tiles, 3 of 11
+    (3, 24, 100, 4, 65, "xstack64", 2),  # the scratch holds 3 groups: 33 + 32 rows; tiles without cells
+    (5, 40, 500, 3, 97, "xstack64", 2),  # one row more than a launch holds: 49 + 48
+    (4, 512, 512, 2, 128, "xstack64", 1),  # a full launch at the widest
+    (3, 320, 260, 3, 190, "xstack64", 2),  # two launches of 6 groups
+    (5, 24, 16, 3, 150, "xstack64", 3),  # narrow cells: the scratch holds fewer groups
+    (9, 24, 32, 3, 20, "xstack32", 1),   # more layers than one launch holds: 5 + 4
+    (3, 40, 130, 1, 60, "xstack32", 1),  # one frame
+    (5, 40, 130, 1, 60, "xstack64", 1),  # one frame in 64-cell tiles
 ]
 
 
-@pytest.mark.parametrize("layers,n_in,H,T,B", GROUP_CASES)
-def test_row_groups_equal_oracle(ql, orc, layers, n_in, H, T, B):
+@pytest.mark.parametrize("layers,n_in,H,T,B,layout,launches", GROUP_CASES)
+def test_row_groups_equal_oracle(ql, orc, layers, n_in, H, T, B, layout, launches):
     from paper_1607_04683_amd.workloads import random_model
     w = random_model(n_in, H, layers, states=40, seed=layers * 1000 + H + B)
     x = np.random.default_rng(B + H).standard_normal((T, B, n_in)).astype(np.float32)
     M = ql.quantize_model(w)
+    assert ql.model_layout(M, T, B) == (layout, launches)
     g = ql.acoustic_model_forward(M, torch.from_numpy(x).cuda(), taps=True)
     o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
     assert_model_taps(g, o, None, names=ql.TAP_NAMES)
 
 
-@pytest.mark.parametrize("B", [3, 100])
-def test_row_groups_carry_state(ql, B):
+@pytest.mark.parametrize("B,layout", [(3, "xrows4"), (20, "xstack32"), (100, "xstack64")])
+def test_row_groups_carry_state(ql, B, layout):
     """Chunks of a sequence with the state carried give the whole call's bits."""
     from paper_1607_04683_amd.workloads import random_model
     M = ql.quantize_model(random_model(40, 100, 5, states=32, seed=B))
@@ -117,6 +125,7 @@ def test_row_groups_carry_state(ql, B):
     whole = ql.acoustic_model_forward(M, x)["post"]
     state, parts = None, []
     for a, b in [(0, 1), (1, 5), (5, 9)]:
+        assert ql.model_layout(M, b - a, B)[0] == layout
         out = ql.empty_state(M, B)
         parts.append(ql.acoustic_model_forward(M, x[a:b].contiguous(), state_in=state,
                                                state_out=out)["post"])
