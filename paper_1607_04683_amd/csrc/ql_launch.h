@@ -213,8 +213,6 @@ hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s,
 // may be used.  *done false when the shapes or the device do not fit that
 // layout (nothing launched).
 size_t xstack_ws(int nl);
-bool xstack_shapes(int nl, int64_t B, int64_t H, int64_t in0, int64_t in1, size_t ws_bytes, int cus,
-                   int lds_max);
 bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max);
 // One batch row on the whole chip (ql_xrow.hip): one XCD per layer.  *done as above.
 hipError_t launch_xrow(const StackArgs &a, size_t ws_bytes, int cus, bool taps, hipStream_t s,

@@ -949,6 +949,28 @@ static bool chip_takes_batch(const StackArgs &a, int cus, int lds_max) {
          stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.nl > 1 ? a.L[1].in : a.H) >= 2;
 }
 
+// Whether a's batch in `launches` launches of 16-row units is faster than what it
+// takes otherwise: k_stack with as many layers a launch as fit the chip, or a
+// launch per layer behind its input product.  One launch always is (at most 5.4 us
+// a frame against 5.5 and more).  Several are a matter of widths: a unit's step
+// costs the same at 16 cells as at 512, where the tiles of the other kernels hold
+// more rows the narrower they are.  us, from runs of 1 to 8 layers of 16 to 500
+// cells, 65 to 1000 rows, 5 and 50 frames (the rule takes the slower side by at
+// most 4% there):
+//   units          per launch 17 + 15.5 a layer (filling the wavefront) + 4.8 a frame
+//   other kernels  per launch 50 + the step's time below a frame
+// 5 layers, 50 frames, units and other: 500 cells, 300 rows (4 launches, a launch
+// per layer) 1415 and 3300; 100 cells, 300 rows (4 launches and 2) 1407 and 860.
+static bool units_pay(const StackArgs &a, int launches) {
+  if (launches <= 1) return true;
+  const int per = a.nl > 1 ? stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.L[1].in) : 1;
+  const int others = (a.nl + per - 1) / per;
+  const double T = (double)a.T, H = (double)a.H, HB = H * (double)a.B;
+  const double step = per > 1 ? 5.0 + 0.003 * H + 1.5e-5 * HB : 7.0 + 0.004 * H + 2.5e-5 * HB;
+  return launches * (17.0 + 15.5 * a.nl + 4.8 * T) - 40.0 <=
+         others * (50.0 + step * T) + (a.nl > 1 ? 5.0 * a.nl : -40.0);
+}
+
 hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s, bool *done) {
   *done = false;
   if (a.T == 0 || a.B == 0 || a.nl < 1 || a.nl > kMaxStack || a.H > 512) return hipSuccess;
@@ -966,6 +988,8 @@ hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s,
   if (a.B == 1) return launch_xrow(a, ws_bytes, cus, tp, s, done);
   e = launch_xrows(a, ws_bytes, cus, tp, s, done);
   if (e != hipSuccess || *done) return e;
+  int cells;
+  if (!units_pay(a, xstack_launches(a, ws_bytes, cus, lds_max, &cells))) return hipSuccess;
   return launch_xstack(a, ws_bytes, cus, lds_max, tp, s, done);
 }
 
@@ -982,7 +1006,7 @@ int stack_chip_path(const StackArgs &a, size_t ws_bytes, int *launches) {
   if (xrows_applies(a, ws_bytes, cus, launches)) return kPathXrows4;
   int cells = 0;
   *launches = xstack_launches(a, ws_bytes, cus, lds_max, &cells);
-  return *launches == 0 ? kPathLayers : cells == 32 ? kPathXstack32 : kPathXstack64;
+  return *launches == 0 || !units_pay(a, *launches) ? kPathLayers : cells == 32 ? kPathXstack32 : kPathXstack64;
 }
 
 hipError_t launch_stack(const StackArgs &a, hipStream_t s, bool *unsupported) {
@@ -1046,14 +1070,19 @@ bool stack_fits_one_launch(const StackArgs &a) {
 }
 
 int stack_layers_routed(int n, int64_t T, int64_t B, int64_t H, int64_t in0, int64_t in1) {
-  int dev = 0, cus = 0, lds_max = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-      hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) {
-    const int nl = std::min(n, kMaxStack);
-    if (B > 1 && xstack_shapes(nl, B, H, in0, in1, stack_ws(nl, T, B, H), cus, lds_max)) return nl;
+  if (B > 1) {
+    StackArgs a{};
+    a.nl = std::min(n, kMaxStack);
+    a.T = T, a.B = B, a.H = H;
+    for (int l = 0; l < a.nl; ++l) {
+      a.L[l].in = l == 0 ? in0 : in1;
+      a.L[l].Wx.ld = round_up(a.L[l].in, 64);
+      a.L[l].Wh.ld = a.L[l].out.ld = round_up(H, 64);
+    }
+    a.L[0].xin.ld = round_up(in0, 64);
+    int launches;
+    if (stack_chip_path(a, stack_ws(a.nl, T, B, H), &launches) != kPathLayers) return a.nl;
   }
-  (void)hipGetLastError();
   return stack_layers_per_launch(n, T, B, H, in0, in1);
 }
 

@@ -705,21 +705,6 @@ constexpr size_t kXsHead = kHeaderBytes + kXsSlotBytes + kXsCounterBytes;
 // (what two row groups of 32 rows in 32-cell tiles per layer take)
 size_t xstack_ws(int nl) { return kXsHead + (size_t)nl * 2 * 90112; }
 
-bool xstack_shapes(int nl, int64_t B, int64_t H, int64_t in0, int64_t in1, size_t ws_bytes, int cus,
-                   int lds_max) {
-  if (nl < 1 || nl > kMaxStack) return false;
-  StackArgs a{};
-  a.nl = nl;
-  a.B = B;
-  a.H = H;
-  for (int l = 0; l < nl; ++l) {
-    a.L[l].in = l == 0 ? in0 : in1;
-    a.L[l].Wx.ld = round_up(a.L[l].in, 64);
-    a.L[l].Wh.ld = a.L[l].out.ld = round_up(H, 64);
-  }
-  return xstack_applies(a, ws_bytes, cus, lds_max);
-}
-
 // The rows from r0 on that one launch takes: 32-cell tiles while the chip (and
 // the scratch) holds enough units for the whole batch, else 64-cell tiles, and
 // then as few launches, of equal size, as the batch needs.

@@ -2,8 +2,9 @@
 chip it runs as a stack of one, with the input product in the step.  Every tap,
 h and the final state against the oracle bit for bit at the edges between that
 layout's kernels (one row; groups of four on up to eight XCDs; units of 16, in
-32- and 64-cell tiles, over several launches), with and without an initial
-state, and for an input too wide for it."""
+32- and 64-cell tiles, over one launch and two), with and without an initial
+state, for narrow cells, which take a launch per layer where several launches of
+units would be slower, and for an input too wide for any of it."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +21,8 @@ def ql():
 
 
 @pytest.mark.parametrize("n_in,H,T,B", [(512, 500, 5, 1), (24, 17, 3, 2), (40, 100, 4, 32), (40, 36, 3, 33),
-                                        (320, 500, 2, 257), (7, 20, 2, 530), (520, 64, 3, 20)])
+                                        (320, 500, 2, 257), (24, 500, 6, 600), (7, 20, 2, 530),
+                                        (520, 64, 3, 20)])
 def test_single_layer_equals_oracle(ql, orc, n_in, H, T, B):
     from paper_1607_04683_amd.workloads import random_model
     w = random_model(n_in, H, 1, seed=H + B)["layers"][0]

@@ -49,16 +49,17 @@ def _model(ql, B, layers=3, H=48, proj=0, seed=1):
     return w, x
 
 
-@pytest.mark.parametrize("B,proj,layout", [(32, 0, "xstack32"), (90, 0, "xstack64"), (1, 0, "xrow"),
-                                           (1, 24, "xrow")])
-def test_layer_wavefront_times_out_and_recovers(ql, B, proj, layout):
-    """Units of 16 rows in tiles of 32 and 64 cells; one row, without and with a
+@pytest.mark.parametrize("layers,B,proj,layout", [(3, 32, 0, "xstack32"), (5, 60, 0, "xstack64"),
+                                                  (3, 90, 0, "spread"), (3, 1, 0, "xrow"),
+                                                  (3, 1, 24, "xrow")])
+def test_layer_wavefront_times_out_and_recovers(ql, layers, B, proj, layout):
+    """Units of 16 rows in tiles of 32 and 64 cells; batched tiles spread over the
+    chip (counters, quantizing workgroups); one row, without and with a
     projection."""
-    w, x = _model(ql, B, proj=proj)
+    w, x = _model(ql, B, layers=layers, proj=proj)
     M = ql.quantize_model(w)
     assert ql.model_layout(M, x.shape[0], B)[0] == layout
-    if B != 90:
-        assert ql.stack_layers_per_launch(M, x.shape[0], B) >= 2
+    assert ql.stack_layers_per_launch(M, x.shape[0], B) >= 2
     ref = ql.acoustic_model_forward(M, x)["post"]
     _times_out(ql, lambda: ql.acoustic_model_forward(M, x))
     assert torch.equal(ql.acoustic_model_forward(M, x)["post"], ref)

@@ -93,11 +93,16 @@ GROUP_CASES = [
     (5, 40, 36, 2, 48, "xstack32", 1),   # the most rows of 5 layers in 32-cell tiles
     (5, 40, 48, 4, 49, "xstack64", 1),   # one row more: 64-cell tiles, 4 groups of 13
     (8, 24, 64, 5, 33, "xstack64", 1),   # 2 groups of 16 at most: 64-cell tiles, 3 of 11
-    (3, 24, 100, 4, 65, "xstack64", 2),  # the scratch holds 3 groups: 33 + 32 rows; tiles without cells
+    (3, 24, 100, 3, 48, "xstack32", 1),  # three full groups; tiles without cells
     (5, 40, 500, 3, 97, "xstack64", 2),  # one row more than a launch holds: 49 + 48
     (4, 512, 512, 2, 128, "xstack64", 1),  # a full launch at the widest
-    (3, 320, 260, 3, 190, "xstack64", 2),  # two launches of 6 groups
-    (5, 24, 16, 3, 150, "xstack64", 3),  # narrow cells: the scratch holds fewer groups
+    (4, 24, 300, 3, 200, "xstack64", 2),  # two launches of 7 groups
+    (5, 40, 400, 3, 200, "xstack64", 3),  # three launches: 67 + 67 + 66 rows
+    # several launches of narrow layers, or of few frames, lose to k_stack
+    (3, 24, 100, 4, 65, "spread", 1),
+    (3, 320, 260, 3, 190, "spread", 1),
+    (5, 24, 16, 3, 150, "spread", 1),
+    (2, 24, 48, 3, 300, "spread", 1),
     (9, 24, 32, 3, 20, "xstack32", 1),   # more layers than one launch holds: 5 + 4
     (3, 40, 130, 1, 60, "xstack32", 1),  # one frame
     (5, 40, 130, 1, 60, "xstack64", 1),  # one frame in 64-cell tiles
@@ -116,11 +121,12 @@ def test_row_groups_equal_oracle(ql, orc, layers, n_in, H, T, B, layout, launche
     assert_model_taps(g, o, None, names=ql.TAP_NAMES)
 
 
-@pytest.mark.parametrize("B,layout", [(3, "xrows4"), (20, "xstack32"), (100, "xstack64")])
-def test_row_groups_carry_state(ql, B, layout):
+@pytest.mark.parametrize("B,H,layout", [(3, 100, "xrows4"), (20, 100, "xstack32"), (100, 100, "spread"),
+                                        (100, 500, "xstack64")])
+def test_row_groups_carry_state(ql, B, H, layout):
     """Chunks of a sequence with the state carried give the whole call's bits."""
     from paper_1607_04683_amd.workloads import random_model
-    M = ql.quantize_model(random_model(40, 100, 5, states=32, seed=B))
+    M = ql.quantize_model(random_model(40, H, 5, states=32, seed=B))
     x = torch.randn(9, B, 40, device="cuda")
     whole = ql.acoustic_model_forward(M, x)["post"]
     state, parts = None, []
