@@ -852,13 +852,13 @@ __global__ __launch_bounds__(256) void k_qmm_small(const float *__restrict__ X, 
 // Per 128 columns (max, sum exp) by one half-wave, lane c holding columns c,
 // c + 32, c + 64 and c + 96; the sums of the two 64-column halves by a
 // butterfly each, added; then the tiles' sums, rescaled to the row's max, in
-// tile order.  The order is fixed, whatever the number of rows.
-constexpr int kSmaxThreads = 1024;
-__global__ __launch_bounds__(kSmaxThreads) void k_smax_rows(float *__restrict__ post, int64_t N,
-                                                            int ntn, float2 *__restrict__ stats,
-                                                            float *__restrict__ logits) {
-  constexpr int HW = kSmaxThreads / 32;
-  __shared__ float smax[kSmaxThreads / 64], sp[1024];
+// tile order.  The order is fixed, whatever the number of rows or of threads.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_smax_rows(float *__restrict__ post, int64_t N, int ntn,
+                                                  float2 *__restrict__ stats,
+                                                  float *__restrict__ logits) {
+  constexpr int HW = NT / 32;
+  __shared__ float smax[NT / 64], sp[NT];
   const int64_t m = blockIdx.x;
   float *y = post + m * N;
   float2 *st = stats + m * ntn;
@@ -894,15 +894,15 @@ __global__ __launch_bounds__(kSmaxThreads) void k_smax_rows(float *__restrict__ 
   if ((tid & 63) == 0) smax[tid >> 6] = rmx;
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kSmaxThreads / 64; ++w) rmx = fmaxf(rmx, smax[w]);
+  for (int w = 0; w < NT / 64; ++w) rmx = fmaxf(rmx, smax[w]);
   float sm = 0.0f;
-  for (int t0 = 0; t0 < ntn; t0 += 1024) {
+  for (int t0 = 0; t0 < ntn; t0 += NT) {
     if (t0 + tid < ntn) {
       const float2 p = st[t0 + tid];
       sp[tid] = p.y * __expf(p.x - rmx);
     }
     __syncthreads();
-    const int n = ntn - t0 < 1024 ? ntn - t0 : 1024;
+    const int n = ntn - t0 < NT ? ntn - t0 : NT;
 #pragma unroll 8
     for (int k = 0; k < n; ++k) sm += sp[k];
     __syncthreads();
@@ -1078,8 +1078,14 @@ hipError_t launch_softmax_layer(const ActRows &X, const WeightMat &W, int64_t M,
     e.acc = acc;
     const hipError_t err = dispatch<EPI_RECOVER>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);
     if (err != hipSuccess || M == 0 || N == 0) return err;
-    hipLaunchKernelGGL(k_smax_rows, dim3((unsigned)M), dim3(kSmaxThreads), 0, s, post, N,
-                       (int)((N + 127) / 128), e.stats, logits);
+    const int ntn = (int)((N + 127) / 128);
+    // threads a row: half a wave per tile where the tiles are few, so that many
+    // rows are in flight; few rows of many tiles take more (product and softmax,
+    // us, with 64, 256, 1024 threads and in the two passes below: 32000 rows x 42
+    // states 27, 44, 142, 52; 2000 x 2000 42, 33, 39, 56; 400 x 4000 34, 19, 16, 57)
+    const int nt = ntn <= 4 ? 64 : ntn <= 32 && M >= 1024 ? 256 : 1024;
+    auto kern = nt == 64 ? k_smax_rows<64> : nt == 256 ? k_smax_rows<256> : k_smax_rows<1024>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)M), dim3(nt), 0, s, post, N, ntn, e.stats, logits);
     return hipGetLastError();
   }
   // many rows: post is written once; two passes of the product instead of

@@ -241,8 +241,11 @@ def test_qmatmul_few_rows(ql, orc, m, rows, cols, gran):
 
 # Row softmax in place: states below, at and above a 128-column tile, more
 # tiles than half-waves, more than one 1024-tile round; rows on either side of
-# the 16-row blocks.
-@pytest.mark.parametrize("m,S", [(1, 1), (3, 127), (16, 128), (17, 129), (5, 4100), (2, 131100)])
+# the 16-row blocks; the last states of 64 threads a row, then 256 and 1024 on
+# either side of their 32 tiles and 1024 rows.
+@pytest.mark.parametrize("m,S", [(1, 1), (3, 127), (16, 128), (17, 129), (5, 4100), (2, 131100),
+                                 (2000, 42), (3, 512), (3, 513), (1024, 513), (1023, 513), (1030, 4096),
+                                 (1024, 4097)])
 def test_softmax_few_rows(ql, orc, m, S):
     from paper_1607_04683_amd.workloads import random_model
     w = random_model(8, 8, 1, states=S, seed=S)
