@@ -39,6 +39,7 @@ struct EpiArgs {
   float2 *stats;  // [M][ntn] (max, sum exp) per column tile
   int ntn;
   const float2 *rowstat;  // [M] (max, 1 / sum exp) per row
+  bool past;              // Y is stored past the caches (see stored_past)
 };
 
 template <int BM, int BN, int BK, int WM, int WN>
@@ -425,7 +426,7 @@ __device__ __forceinline__ void row_reduce(float (&v)[N]) {
 // staged once.  Softmax statistics are reduced per wave over its TN columns
 // (max, then sum of exp(y - max)) and the WN partials of a row are merged
 // with the usual rescaling.
-template <class C, int EPI>
+template <class C, int EPI, bool PAST>
 __device__ __forceinline__ void recover_epilogue_lds(const EpiArgs &e, int64_t M, int64_t N,
                                                      int64_t K, int64_t m0, int64_t n0, int tn,
                                                      int wm, int wn, int lane, char *smem,
@@ -507,11 +508,9 @@ __device__ __forceinline__ void recover_epilogue_lds(const EpiArgs &e, int64_t M
         }
         if (m < M) {
           if (vec) {
-            // hundreds of MB to GBs of output that nothing in this launch reads:
-            // kept out of the caches the operands' panels live in (51200 x
-            // 8192 x 512 with its recurrence 3330 -> 3260 us, 64000 x 8192
-            // posteriors with theirs 6155 -> 6105)
-            __builtin_nontemporal_store(v4f{y[0], y[1], y[2], y[3]}, reinterpret_cast<v4f *>(e.Y + off));
+            const v4f v = {y[0], y[1], y[2], y[3]};
+            if constexpr (PAST) __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(e.Y + off));
+            else *reinterpret_cast<v4f *>(e.Y + off) = v;
           } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -637,7 +636,12 @@ __global__ __launch_bounds__(64 * WM *WN) void k_gemm(const int8_t *__restrict__
     if constexpr (EPI == EPI_RAW)
       raw_epilogue_lds<C>(e, M, N, K, m0, n0, wm, wn, lane, smem, acc);
     else
-      recover_epilogue_lds<C, EPI>(e, M, N, K, m0, n0, tn, wm, wn, lane, smem, rowmax, rowinv, acc);
+      if (EPI != EPI_SMAX_STATS && e.past)
+        recover_epilogue_lds<C, EPI, EPI != EPI_SMAX_STATS>(e, M, N, K, m0, n0, tn, wm, wn, lane, smem,
+                                                            rowmax, rowinv, acc);
+      else
+        recover_epilogue_lds<C, EPI, false>(e, M, N, K, m0, n0, tn, wm, wn, lane, smem, rowmax, rowinv,
+                                            acc);
     return;
   }
 
@@ -1003,12 +1007,23 @@ static EpiArgs make_epi(const ActRows &X, const WeightMat &W, const float *bias)
   return e;
 }
 
+// Whether the fp32 results of a large product go past the caches: more of them than
+// the memory-side cache (256 MB) holds would only push out the operands' panels,
+// fewer are still there for the kernel that reads them next.  us through the
+// caches and past them: 2048 cells with 512 projected units, 256 rows, product and
+// recurrence, 24 frames (201 MB) 450 and 467, 48 frames (403 MB) 858 and 853, 200
+// frames 3318 and 3270; product 4096 x 8192 x 512 (134 MB) 46 and 55, 16384 rows
+// (537 MB) 206 and 178; a forward with 8192 posteriors of 8192 frames (268 MB) 731
+// and 742, 64000 frames 5200 and 5140.
+static bool stored_past(int64_t M, int64_t N) { return M * N * 4 > (int64_t)256 << 20; }
+
 hipError_t launch_gemm_recover(const ActRows &X, const WeightMat &W, int64_t M, int64_t N,
                                int64_t K, const float *bias, float *Y, int32_t *acc,
                                hipStream_t s) {
   EpiArgs e = make_epi(X, W, bias);
   e.Y = Y;
   e.acc = acc;
+  e.past = stored_past(M, N);
   return dispatch<EPI_RECOVER>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);
 }
 
@@ -1104,6 +1119,7 @@ hipError_t launch_softmax_layer(const ActRows &X, const WeightMat &W, int64_t M,
   e.acc = nullptr;
   e.logits = nullptr;
   e.Y = post;
+  e.past = stored_past(M, N);
   return dispatch<EPI_SMAX_OUT>(X.codes, X.ld, W.codes, W.ld, M, N, K, e, s);
 }
 

@@ -287,3 +287,18 @@ def test_qmatmul_on_its_input(ql, m, rows, cols, gran, what, offset):
     y, acc = (got, apart) if what == "Y" else (apart.view(torch.float32), got.view(torch.int32))
     assert torch.equal(y.view(torch.int32), want_y.reshape(-1).view(torch.int32))
     assert torch.equal(acc, want_acc.reshape(-1))
+
+
+@pytest.mark.parametrize("m,rows", [(8192, 8192), (8193, 8192), (8200, 8190)])
+def test_qmatmul_results_on_both_sides_of_the_caches(ql, m, rows):
+    """256 MB of results, and more, which are stored past the caches; with rows
+    that are no multiple of 16 bytes.  Per-row quantization makes a row's result
+    its own, so rows are compared with their product alone, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    W = ql.quantize(torch.randn(rows, 96, generator=g, device="cuda"))
+    X = torch.randn(m, 96, generator=g, device="cuda")
+    bias = torch.randn(rows, generator=g, device="cuda")
+    y, _ = ql.quantized_matmul(W, X, ql.QL_ACT_PER_ROW, bias)
+    idx = torch.tensor([0, 1, 255, 256, 4097, m - 2, m - 1], device="cuda")
+    want, _ = ql.quantized_matmul(W, X[idx].contiguous(), ql.QL_ACT_PER_ROW, bias)
+    assert torch.equal(y[idx].view(torch.int32), want.view(torch.int32))
