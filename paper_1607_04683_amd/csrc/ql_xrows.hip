@@ -543,11 +543,17 @@ static XvPlan plan_xrows(const Args &a, size_t word_bytes, int cus) {
   // projection 3.5 in fours against 4.7 in k_xstack, in eights no faster than
   // that, so fours in one launch only.  With P = 200, 5.5 in fours and 7.4 a
   // launch in eights, against 39-43 with one launch per layer (31-35 for 4
-  // layers), about 8 a layer: as many launches as layers still pay.
+  // layers).
   const int64_t most = (int64_t)groups * (PROJ ? 8 : 4);
   p.launches = (a.B + most - 1) / most;
   p.chunk = (a.B + p.launches - 1) / p.launches;
   if (p.launches > (PROJ ? a.nl : 1)) return p;
+  // Several launches each fill the wavefront anew, 18 us a layer, for 6.2 a frame;
+  // a launch per layer (from 16 rows on k_xrec) costs 30 us and 7.2 a frame.
+  // 5 x 500, P = 200, 40 rows (5 launches), us so and with a launch per layer: 12
+  // frames 1000 and 721, 30 frames 1569 and 1409, 100 frames 3762 and 4061; 32
+  // rows (4 launches), 12 frames 817 and 713.
+  if (p.launches > 1 && p.launches * (18.0 * a.nl + 6.2 * a.T) > a.nl * (30.0 + 7.2 * a.T)) return p;
   const int nr = p.chunk <= 4 * groups ? 4 : 8;
   const int ng = (int)((p.chunk + nr - 1) / nr);
   p.tl.rows = (int)((p.chunk + ng - 1) / ng);

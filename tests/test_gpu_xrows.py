@@ -44,7 +44,8 @@ def ql():
     (2, 512, 512, 512, 20, 27, "xrows8", 1),  # every tile full; groups of 7, 7, 7 and 6 rows
     (8, 40, 33, 17, 12, 20, "xrows8", 3),    # launches of 7, 7 and 6 rows
     (4, 16, 100, 40, 12, 31, "xrows8", 2),   # launches of 16 and 15 rows, two groups each
-    # elsewhere
+    # elsewhere: more rows than a launch holds without a projection; too little
+    # space for the words; too few frames for several launches
     (5, 40, 100, 0, 1, 5, "xstack32", 1),
     (5, 40, 33, 0, 6, 8, "xstack32", 1),
     (4, 24, 17, 0, 2, 9, "xstack32", 1),
@@ -55,6 +56,7 @@ def ql():
     (2, 512, 512, 512, 3, 8, "layers", 2),
     (8, 40, 33, 17, 5, 20, "layers", 8),
     (4, 16, 100, 40, 2, 33, "layers", 4),
+    (5, 40, 100, 24, 12, 40, "layers", 5),
 ])
 def test_rows_equal_oracle(ql, orc, layers, n_in, H, P, T, B, layout, launches):
     from paper_1607_04683_amd.workloads import random_model
@@ -72,7 +74,8 @@ def test_rows_equal_oracle(ql, orc, layers, n_in, H, P, T, B, layout, launches):
 @pytest.mark.parametrize("P,B,cuts,layouts", [
     (0, 3, (0, 1, 5, 9), ("xrows4", "xrows4", "xrows4")),
     (24, 7, (0, 1, 5, 9), ("layers", "layers", "layers")),
-    (24, 40, (0, 1, 5, 9), ("xrows8", "xrows8", "xrows8")),
+    (24, 40, (0, 1, 5, 9), ("layers", "layers", "layers")),
+    (24, 40, (0, 64, 65, 140), ("xrows8", "layers", "xrows8")),
     (24, 3, (0, 1, 13, 30), ("layers", "xrows4", "xrows4")),
     (24, 7, (0, 12, 13, 30), ("xrows8", "layers", "xrows8")),
 ])
