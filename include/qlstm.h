@@ -434,6 +434,12 @@ int32_t ql_debug_stack_layout(const ql_lstm_layer *layers, int32_t n, int64_t T,
  * those layers take, each over a part of the batch (one per layer where the
  * result is 0).  -1 for an invalid model, T < 0 or B < 0. */
 int32_t ql_debug_model_layout(const ql_model *M, int64_t T, int64_t B, int32_t *launches);
+/* Test hook: over how many launches the fp32 recurrence of a layer of H cells
+ * without a projection (backward 0), or the backward recurrence of the training
+ * step (1), runs T frames of B rows with a part of the batch on each XCD of the
+ * current device; 0: as tiles over the whole chip (or not at all).  -1 for H < 1,
+ * T < 0 or B < 0. */
+int32_t ql_debug_float_layout(int32_t backward, int64_t H, int64_t T, int64_t B);
 /* Elementwise gate functions on device arrays (fn 0 = e^x, 1 = sigmoid,
  * 2 = tanh, 3 = the reciprocal 1 / d that sigmoid applies to d = 1 + e^-x,
  * defined for d in [1, 2^126) and equal there to IEEE division) -- the exact

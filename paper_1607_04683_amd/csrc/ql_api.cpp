@@ -1144,6 +1144,17 @@ int32_t ql_debug_model_layout(const ql_model *M, int64_t T, int64_t B, int32_t *
   if (path == kPathLayers) nlaunch = 1;
   return path == kPathLayers ? kPathSpread : path;
 }
+int32_t ql_debug_float_layout(int32_t backward, int64_t H, int64_t T, int64_t B) {
+  if (H < 1 || T < 0 || B < 0) return -1;
+  int dev = 0, cus = 0, lds = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return backward ? xbptt_launches(H, T, B, cus, lds) : xrec_f32_launches(H, T, B, cus, lds);
+}
 int32_t ql_debug_recurrence_layout(const ql_lstm_layer *L, int64_t B) {
   if (check_layer(L) != QL_OK || B < 0) return -1;
   ActBuf out{};

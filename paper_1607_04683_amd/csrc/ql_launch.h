@@ -278,6 +278,8 @@ hipError_t launch_recurrent_f32(const F32RecArgs &a, hipStream_t s, bool *unsupp
 // an eighth of the batch.  *done false when the shapes or the device do not
 // fit that layout (nothing launched).
 hipError_t launch_xrec_f32(const F32RecArgs &a, int cus, int lds_max, hipStream_t s, bool *done);
+// How many launches that layout takes such a layer in; 0: none.
+int xrec_f32_launches(int64_t H, int64_t T, int64_t B, int cus, int lds_max);
 
 // ---- quantization-aware training step (ql_train.hip)
 // Cross-entropy of the posteriors post [N][S] against targets [N]: dC/dz =
@@ -307,5 +309,6 @@ hipError_t launch_bptt(const BpttArgs &a, hipStream_t s, bool *unsupported);
 // (nothing launched).
 size_t xbptt_ws(int64_t B);
 hipError_t launch_xbptt(const BpttArgs &a, int cus, int lds_max, hipStream_t s, bool *done);
+int xbptt_launches(int64_t H, int64_t T, int64_t B, int cus, int lds_max);
 
 }  // namespace ql

@@ -298,10 +298,17 @@ static hipError_t run_xbptt(const BpttArgs &a, const XbTiling &tl, int cus, hipS
                                     kargs, (unsigned)lds, s);
 }
 
+// Launches the layout takes a in; 0: it does not take a.
+static int plan_xbptt(const BpttArgs &a, int cus, int lds_max) {
+  if (cus != kXbXcds * kXbSlots || lds_max < 100 * 1024) return 0;
+  if (a.H < 1 || a.H > kXbMaxH || a.B < 1 || a.T < 1) return 0;
+  const int64_t most = kXbXcds * kXbMaxRows, launches = (a.B + most - 1) / most;
+  return (int)launches;
+}
+
 hipError_t launch_xbptt(const BpttArgs &a, int cus, int lds_max, hipStream_t s, bool *done) {
   *done = false;
-  if (cus != kXbXcds * kXbSlots || lds_max < 100 * 1024) return hipSuccess;
-  if (a.H < 1 || a.H > kXbMaxH || a.B < 1 || a.T < 1) return hipSuccess;
+  if (plan_xbptt(a, cus, lds_max) == 0) return hipSuccess;
   int64_t chunk;
   const int rows = rows_per_xcd(a.B, &chunk);
   for (int64_t r0 = 0; r0 < a.B; r0 += chunk) {
@@ -312,6 +319,12 @@ hipError_t launch_xbptt(const BpttArgs &a, int cus, int lds_max, hipStream_t s, 
     if (e != hipSuccess || !*done) return e;
   }
   return hipSuccess;
+}
+
+int xbptt_launches(int64_t H, int64_t T, int64_t B, int cus, int lds_max) {
+  BpttArgs a{};
+  a.H = H, a.T = T, a.B = B;
+  return plan_xbptt(a, cus, lds_max);
 }
 
 hipError_t set_wait_bound_xbptt(int polls) { return set_wait_bound_here(polls); }

@@ -87,12 +87,26 @@ __global__ __launch_bounds__(kXfThreads) void k_xrec_f32(F32RecArgs a, XfTiling 
   // W_h: lane 4 c + g holds gate g of cell c, its k from kw on
   const int kpw = (int)((H + 4 * kXfWaves - 1) / (4 * kXfWaves)) * 4;  // k per wave, <= 64
   const int kw = wave * kpw;
+  // (no load depends on the lane, so that all are in flight at once: loads of
+  // single floats behind tests of the lane's k came in 10 us later at 500 cells;
+  // what lies past the ends is dropped)
   float w[64];
   {
     const int64_t j = j0 + (lane >> 2);
     const float *src = a.Wh + ((lane & 3) * H + (j < H ? j : H - 1)) * H;
+    if (H % 4 == 0 && ((uintptr_t)a.Wh & 15) == 0) {  // rows 16-byte aligned
+      v4f v[16];
 #pragma unroll
-    for (int k = 0; k < 64; ++k) w[k] = k < kpw && kw + k < H ? src[kw + k] : 0.0f;
+      for (int q = 0; q < 16; ++q)
+        v[q] = 4 * q < kpw ? *reinterpret_cast<const v4f *>(src + std::min<int64_t>(kw + 4 * q, H - 4)) : v4f{};
+#pragma unroll
+      for (int k = 0; k < 64; ++k) w[k] = kw + k < H ? v[k / 4][k % 4] : 0.0f;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 64; ++k) w[k] = k < kpw ? src[std::min<int64_t>(kw + k, H - 1)] : 0.0f;
+#pragma unroll
+      for (int k = 0; k < 64; ++k) w[k] = kw + k < H ? w[k] : 0.0f;
+    }
   }
   for (int i = tid; i < NR * kXfLdx; i += kXfThreads) xs[i] = 0.0f;  // rows and k past the end
 
@@ -241,15 +255,28 @@ static hipError_t run_xf32(const F32RecArgs &a, const XfTiling &tl, int cus, hip
                                     kargs, (unsigned)lds, s);
 }
 
+// Launches the layout takes a in (up to 16 rows per XCD, as few of equal size as
+// that allows); 0: a runs as tiles of the batch over the chip, whose sums are in
+// another order (so the choice may not depend on T: chunks of a sequence chain
+// with the bits of the whole).  A further launch's steps take as long whatever the
+// width, where tiles hold more rows of narrow layers.  50 frames, us, in tiles and
+// so: 64 cells, 300 rows 329 and 630; 200 cells, 200 rows 616 and 593, 300 rows 646
+// and 840; 256 cells, 500 rows 955 and 1148; 280 cells 1992 and 1227; 400 cells,
+// 300 rows 1882 and 1005 (5 frames 290 and 273; 280 cells 207 and 253).
+static int plan_xf32(const F32RecArgs &a, int cus, int lds_max) {
+  if (cus != kXfXcds * kXfSlots || lds_max < 100 * 1024) return 0;
+  if (a.P > 0 || a.H < 1 || a.H > kXfMaxH || a.B < 1 || a.T < 1) return 0;
+  const int64_t most = kXfXcds * kXfMaxRows, launches = (a.B + most - 1) / most;
+  return launches == 1 || a.H > (launches == 2 ? 200 : 256) ? (int)launches : 0;
+}
+
 // The exchange words, [2][B][H] of 8 bytes, are what recurrent_f32_ws holds
 // for a layer without a projection.
 hipError_t launch_xrec_f32(const F32RecArgs &a, int cus, int lds_max, hipStream_t s, bool *done) {
   *done = false;
-  if (cus != kXfXcds * kXfSlots || lds_max < 100 * 1024) return hipSuccess;
-  if (a.P > 0 || a.H < 1 || a.H > kXfMaxH || a.B < 1 || a.T < 1) return hipSuccess;
-  // up to 16 rows per XCD, in as few launches of equal size as that allows
-  const int64_t most = kXfXcds * kXfMaxRows;
-  const int64_t launches = (a.B + most - 1) / most, chunk = (a.B + launches - 1) / launches;
+  const int64_t launches = plan_xf32(a, cus, lds_max);
+  if (launches == 0) return hipSuccess;
+  const int64_t chunk = (a.B + launches - 1) / launches;
   for (int64_t r0 = 0; r0 < a.B; r0 += chunk) {
     XfTiling tl{r0, std::min(a.B, r0 + chunk), 0};
     tl.rows = (int)((tl.r1 - tl.r0 + kXfXcds - 1) / kXfXcds);
@@ -259,6 +286,12 @@ hipError_t launch_xrec_f32(const F32RecArgs &a, int cus, int lds_max, hipStream_
     if (e != hipSuccess || !*done) return e;
   }
   return hipSuccess;
+}
+
+int xrec_f32_launches(int64_t H, int64_t T, int64_t B, int cus, int lds_max) {
+  F32RecArgs a{};
+  a.H = H, a.T = T, a.B = B;
+  return plan_xf32(a, cus, lds_max);
 }
 
 hipError_t set_wait_bound_xf32(int polls) { return set_wait_bound_here(polls); }

@@ -37,7 +37,7 @@ EXPORTS = [
     "ql_acoustic_model_forward_frames", "ql_acoustic_model_forward_stream",
     "ql_acoustic_model_forward_stream_noalloc", "ql_train_step_workspace", "ql_train_step",
     "ql_debug_set_wait_bound", "ql_debug_recurrence_layout", "ql_debug_stack_layout",
-    "ql_debug_model_layout",
+    "ql_debug_model_layout", "ql_debug_float_layout",
 ]
 
 
@@ -148,6 +148,8 @@ def load(path: str = LIB_PATH):
     L.ql_debug_stack_layout.restype = i32
     L.ql_debug_model_layout.argtypes = [C.POINTER(CModel), i64, i64, C.POINTER(i32)]
     L.ql_debug_model_layout.restype = i32
+    L.ql_debug_float_layout.argtypes = [i32, i64, i64, i64]
+    L.ql_debug_float_layout.restype = i32
     L.ql_f32_matmul.argtypes = [vp, i64, i64, vp, i64, vp, vp, vp]
     L.ql_quantize_activations.argtypes = [vp, i64, i64, C.POINTER(CQAct), vp]
     L.ql_lstm_stack_workspace.argtypes = [C.POINTER(CLayer), i32, i64, i64]
@@ -850,3 +852,9 @@ def model_layout(M: Model, T: int, B: int) -> tuple[str, int]:
     if k < 0:
         raise ValueError("no layout: invalid model, T or B")
     return MODEL_LAYOUTS[k], n.value
+
+
+def float_layout(H: int, T: int, B: int, backward: bool = False) -> int:
+    """Launches in which the fp32 recurrence (or the training step's backward one)
+    runs with a part of the batch on each XCD; 0: as tiles over the chip."""
+    return int(load().ql_debug_float_layout(int(backward), H, T, B))

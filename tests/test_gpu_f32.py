@@ -112,16 +112,37 @@ def test_f32_model_B64_sampled_utterance(ql, orc):
     assert np.max(np.abs(g - o)) <= TOL
 
 
-@pytest.mark.parametrize("H,T,B", [
-    (1, 3, 1),       # one cell, one row
-    (15, 2, 8),      # a tile one cell short; one row on every XCD
-    (17, 4, 9),      # a second tile of one cell; 2 rows, the last XCDs without
-    (512, 2, 33),    # every tile full; 5 rows: a second row group of one
-    (500, 3, 64),    # 8 rows per XCD
-    (96, 1, 65),     # 9 rows: the 16-row form; one frame
-    (260, 3, 128),   # a full launch
-    (36, 3, 129),    # one row more than a launch holds
+# The last column: launches of the layout with an eighth of the batch per XCD (0: the
+# batch in tiles over the chip, where several launches of narrow layers are slower).
+@pytest.mark.parametrize("H,T,B,launches", [
+    (1, 3, 1, 1),       # one cell, one row
+    (15, 2, 8, 1),      # a tile one cell short; one row on every XCD
+    (17, 4, 9, 1),      # a second tile of one cell; 2 rows, the last XCDs without
+    (512, 2, 33, 1),    # every tile full; 5 rows: a second row group of one
+    (500, 3, 64, 1),    # 8 rows per XCD
+    (487, 3, 20, 1),    # rows of W_h off the 16-byte boundaries
+    (96, 1, 65, 1),     # 9 rows: the 16-row form; one frame
+    (260, 3, 128, 1),   # a full launch
+    (36, 3, 129, 0),    # one row more than a launch holds
+    (200, 2, 129, 0),
+    (201, 3, 129, 2),   # launches of 65 and 64 rows
+    (256, 2, 257, 0),
+    (257, 2, 257, 3),
 ])
-def test_f32_layer_xcd_rows(ql, orc, H, T, B):
+def test_f32_layer_xcd_rows(ql, orc, H, T, B, launches):
     """The layout with an eighth of the batch per XCD at its edges."""
+    assert ql.float_layout(H, T, B) == launches
     _layer(ql, orc, 24, H, 0, T, B, seed=H + T + B, h0c0=B % 2 == 1)
+
+
+@pytest.mark.parametrize("H,B", [(500, 3), (300, 140), (64, 140)])
+def test_f32_layer_chunks_chain_bit_for_bit(ql, H, B):
+    from paper_1607_04683_amd.workloads import random_model
+    L = ql.f32_layer(random_model(24, H, 1, seed=H)["layers"][0])
+    x = torch.randn(9, B, 24, device="cuda")
+    whole, h, c, parts = ql.f32_lstm_layer_forward(L, x), None, None, []
+    for a, b in [(0, 1), (1, 3), (3, 9)]:
+        g = ql.f32_lstm_layer_forward(L, x[a:b].contiguous(), h, c)
+        h, c = g["hT"], g["cT"]
+        parts.append(g["h"])
+    assert torch.equal(torch.cat(parts), whole["h"]) and torch.equal(c, whole["cT"])
