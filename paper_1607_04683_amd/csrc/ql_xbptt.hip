@@ -298,12 +298,17 @@ static hipError_t run_xbptt(const BpttArgs &a, const XbTiling &tl, int cus, hipS
                                     kargs, (unsigned)lds, s);
 }
 
-// Launches the layout takes a in; 0: it does not take a.
+// Launches the layout takes a in; 0: a runs faster, or only, on k_bptt, which has
+// the whole batch in one.  A second launch pays for narrow layers and for few
+// steps (where start-up counts), a third never.  A training step of one layer, us,
+// k_bptt and so: 64 cells, 200 rows, 100 frames 2310 and 2265; 128 cells the same
+// 2448 and 2539, 20 frames 1053 and 1016; 64 cells, 300 rows, 100 frames 2490 and
+// 2909, 20 frames 1036 and 1083.
 static int plan_xbptt(const BpttArgs &a, int cus, int lds_max) {
   if (cus != kXbXcds * kXbSlots || lds_max < 100 * 1024) return 0;
   if (a.H < 1 || a.H > kXbMaxH || a.B < 1 || a.T < 1) return 0;
   const int64_t most = kXbXcds * kXbMaxRows, launches = (a.B + most - 1) / most;
-  return (int)launches;
+  return launches == 1 || (launches == 2 && (a.H <= 64 || a.T <= 40)) ? (int)launches : 0;
 }
 
 hipError_t launch_xbptt(const BpttArgs &a, int cus, int lds_max, hipStream_t s, bool *done) {

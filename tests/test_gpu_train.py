@@ -133,10 +133,15 @@ def test_train_step_rejects_projection_layers(ql):
 
 # The backward recurrence with an eighth of the batch per XCD, at its edges:
 # two frames; a tile of one cell; 1, 4, 5, 8 and 9 rows per XCD (the last XCDs
-# short or empty); one row more than a launch holds; every tile full.
-@pytest.mark.parametrize("H,T,B", [(16, 2, 4), (17, 6, 9), (33, 5, 32), (500, 4, 33), (500, 3, 64),
-                                   (36, 4, 65), (40, 3, 129), (512, 3, 7)])
-def test_train_backward_xcd_rows(ql, orc, H, T, B):
+# short or empty); one row more than a launch holds; every tile full; and where
+# k_bptt takes over: a second launch of wider layers over more than 40 frames, a
+# third of any.
+@pytest.mark.parametrize("H,T,B,launches", [(16, 2, 4, 1), (17, 6, 9, 1), (33, 5, 32, 1), (500, 4, 33, 1),
+                                            (500, 3, 64, 1), (36, 4, 65, 1), (40, 3, 129, 2),
+                                            (512, 3, 7, 1), (64, 41, 129, 2), (65, 40, 129, 2),
+                                            (65, 41, 129, 0), (24, 3, 257, 0)])
+def test_train_backward_xcd_rows(ql, orc, H, T, B, launches):
+    assert ql.float_layout(H, T, B, backward=True) == launches
     w, x, y = _case(24, H, 2, 40, T, B, seed=H + T + B)
     _compare(ql, orc, w, x, y, lr=0.5, quantize_output=True)
 
