@@ -256,20 +256,21 @@ __global__ __launch_bounds__(256) void k_softmax_rows(float *x, int64_t S) {
 // once, written once (6400 x 8192: 150 us in three passes over the row,
 // 64 us so).
 constexpr int kSmaxRegs = 32;
+template <int R>
 __global__ __launch_bounds__(256) void k_softmax_rows_reg(float *x, int64_t S) {
   __shared__ float red[4];
   float *row = x + (int64_t)blockIdx.x * S;
-  float v[kSmaxRegs], mx = -INFINITY, sm = 0.0f;
+  float v[R], mx = -INFINITY, sm = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kSmaxRegs; ++i) {
+  for (int i = 0; i < R; ++i) {
     const int64_t k = threadIdx.x + 256 * i;
     v[i] = k < S ? row[k] : -INFINITY;
   }
 #pragma unroll
-  for (int i = 0; i < kSmaxRegs; ++i) mx = fmaxf(mx, v[i]);
+  for (int i = 0; i < R; ++i) mx = fmaxf(mx, v[i]);
   mx = block_reduce(mx, true, red);
 #pragma unroll
-  for (int i = 0; i < kSmaxRegs; ++i)
+  for (int i = 0; i < R; ++i)
     if (threadIdx.x + 256 * i < S) {
       v[i] = __expf(v[i] - mx);
       sm += v[i];
@@ -277,14 +278,23 @@ __global__ __launch_bounds__(256) void k_softmax_rows_reg(float *x, int64_t S) {
   sm = block_reduce(sm, false, red);
   const float inv = 1.0f / sm;
 #pragma unroll
-  for (int i = 0; i < kSmaxRegs; ++i)
+  for (int i = 0; i < R; ++i)
     if (threadIdx.x + 256 * i < S) row[threadIdx.x + 256 * i] = v[i] * inv;
 }
 
 hipError_t launch_softmax_rows(float *x, int64_t rows, int64_t S, hipStream_t s) {
   if (rows == 0 || S == 0) return hipSuccess;
   if (S <= 256 * kSmaxRegs) {
-    hipLaunchKernelGGL(k_softmax_rows_reg, dim3((unsigned)rows), dim3(256), 0, s, x, S);
+    // registers for the row and no more (100 000 rows of 64 states, us, in the
+    // three passes below, with 32 registers a thread, and so: 99, 316, 83; 50 000
+    // of 1000 125, 165, 61)
+    auto kern = S <= 256    ? k_softmax_rows_reg<1>
+                : S <= 512  ? k_softmax_rows_reg<2>
+                : S <= 1024 ? k_softmax_rows_reg<4>
+                : S <= 2048 ? k_softmax_rows_reg<8>
+                : S <= 4096 ? k_softmax_rows_reg<16>
+                            : k_softmax_rows_reg<kSmaxRegs>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(256), 0, s, x, S);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_softmax_rows, dim3((unsigned)rows), dim3(256), 0, s, x, S);

@@ -146,3 +146,17 @@ def test_f32_layer_chunks_chain_bit_for_bit(ql, H, B):
         h, c = g["hT"], g["cT"]
         parts.append(g["h"])
     assert torch.equal(torch.cat(parts), whole["h"]) and torch.equal(c, whole["cT"])
+
+
+# Row softmax: states around the registers per thread it is built for, and the
+# first width beyond them all.
+@pytest.mark.parametrize("S", [1, 63, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
+def test_f32_posteriors_at_the_softmax_widths(ql, orc, S):
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(8, 8, 1, states=S, seed=S)
+    x = np.random.default_rng(S).standard_normal((3, 2, 8)).astype(np.float32)
+    g = ql.f32_acoustic_model_forward(ql.f32_model(w), dev(x))["post"].cpu().numpy().astype(np.float64)
+    o = orc.acoustic_model_forward_f32(w, x)["post"]
+    # exp of a difference of logits |z| < 8 and fp32 sums of S terms
+    assert np.max(np.abs(g - o)) <= TOL * np.max(o)
+    assert np.max(np.abs(g.sum(-1) - 1.0)) < 1e-5
