@@ -807,7 +807,24 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_gemm_skinny(
 // itself (per tensor, or per row), into LDS, and multiplies its 64 rows of W'.
 // At these sizes a launch costs more than reading X again (16 x 256 x 128 per
 // tensor: two launches 14.3 us a call, one 9.7).
-constexpr int kSmallValues = 8192, kSmallRows = 64;
+constexpr int kSmallValues = 8192;
+// Whether one launch is the faster form.  Every workgroup has four waves for the
+// rows, one at a time each (per row: range and params too, one after the other), so
+// few rows, fewer per row, where rows off the 16-byte boundaries, which come in
+// single floats, weigh more; and many rows only while the workgroups, which all
+// repeat that, are few.  rows x K x outputs, us in two launches and in one: per row
+// 24 x 64 x 8192 12.4 and 9.0, 32 x 64 x 65536 14.4 and 18.4, 64 x 128 x 8192 12.4
+// and 18.9, 16 x 511 x 8192 12.0 and 13.4, x 200000 67 and 52; per tensor 64 x 128 x
+// 8192 12.4 and 12.8, x 32768 22.3 and 15.0, x 65536 19.1 and 21.1, 32 x 64 x 200000
+// 44.8 and 29.7, 48 x 170 x 8192 12.7 and 14.7.
+static bool small_product(const float *X, bool per_row, int64_t M, int64_t N, int64_t K) {
+  if (M < 1 || N < 1 || M * K > kSmallValues) return false;
+  if (K % 4 != 0 || ((uintptr_t)X & 15) != 0) {
+    if (!per_row) return M <= 24;
+    return M <= 4 || (M <= 16 && (M * K <= 4096 || N > 32768));
+  }
+  return M <= (per_row ? 24 : 32) || (M <= (per_row ? 32 : 64) && N <= 32768);
+}
 template <int MB, bool PER_ROW>
 __global__ __launch_bounds__(256) void k_qmm_small(const float *__restrict__ X, int64_t M,
                                                    const int8_t *__restrict__ B, int64_t ldb, int64_t N,
@@ -1030,14 +1047,15 @@ hipError_t launch_gemm_recover(const ActRows &X, const WeightMat &W, int64_t M, 
 hipError_t launch_qmm_small(const float *X, bool per_row, const WeightMat &W, int64_t M, int64_t N,
                             int64_t K, const float *bias, float *Y, int32_t *acc, hipStream_t s,
                             bool *done) {
-  *done = M > 0 && N > 0 && M <= kSmallRows && M * K <= kSmallValues;
+  *done = small_product(X, per_row, M, N, K);
   if (!*done) return hipSuccess;
   EpiArgs e = make_epi(ActRows{}, W, bias);
   e.Y = Y;
   e.acc = acc;
-  const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-  auto kern = per_row ? (mb == 1 ? k_qmm_small<1, true> : mb == 2 ? k_qmm_small<2, true> : k_qmm_small<4, true>)
-                      : (mb == 1 ? k_qmm_small<1, false> : mb == 2 ? k_qmm_small<2, false> : k_qmm_small<4, false>);
+  auto kern = per_row    ? (M <= 16 ? k_qmm_small<1, true> : k_qmm_small<2, true>)
+              : M <= 16 ? k_qmm_small<1, false>
+              : M <= 32 ? k_qmm_small<2, false>
+                        : k_qmm_small<4, false>;
   const size_t lds = (size_t)M * (size_t)(round_up(K, 64) + 16);
   hipLaunchKernelGGL(kern, dim3((unsigned)((N + 63) / 64)), dim3(256), lds, s, X, M, W.codes, W.ld, N, K, e);
   return hipGetLastError();

@@ -231,9 +231,12 @@ def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
 # columns one off its 16, K around its 64-byte steps and its unrolled 512.
 @pytest.mark.parametrize("m,rows,cols", [(1, 15, 63), (16, 17, 64), (17, 33, 65), (32, 100, 511),
                                          (33, 31, 512), (64, 16, 513), (65, 130, 577), (200, 4, 1100),
-                                         # one launch up to 8192 values and 64 rows of X
+                                         # one launch up to 8192 values: 16, 24, 32 and 64
+                                         # rows of X, aligned and not
                                          (64, 100, 128), (64, 65, 129), (1, 300, 8192), (1, 17, 8193),
-                                         (17, 129, 481), (32, 64, 255)])
+                                         (17, 129, 481), (32, 64, 255), (24, 65, 340), (25, 65, 325),
+                                         (32, 70, 256), (33, 70, 248), (16, 40, 255), (16, 40, 257),
+                                         (24, 32772, 64), (25, 32772, 64), (40, 32768, 64)])
 @pytest.mark.parametrize("gran", [0, 1])
 def test_qmatmul_few_rows(ql, orc, m, rows, cols, gran):
     test_qmatmul_ragged_shapes(ql, orc, m, rows, cols, 1, gran)
