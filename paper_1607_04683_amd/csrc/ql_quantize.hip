@@ -19,8 +19,6 @@
 
 namespace ql {
 
-constexpr int kEncodeRows = 16;  // rows of one block of k_set_encode
-
 // One wave quantizes one vector: min/max, params, codes, code sum.
 template <class Row>
 __device__ __forceinline__ void quantize_row_wave(const Row &x, int64_t K, int64_t row,
@@ -126,7 +124,7 @@ __device__ __forceinline__ void put_set_params(const QParams &p, int64_t s, cons
 __global__ __launch_bounds__(256) void k_set_encode(const float *__restrict__ X, int64_t rps,
                                                     int64_t cols,
                                                     const float2 *__restrict__ part, int nparts,
-                                                    SetOut o) {
+                                                    int brows, SetOut o) {
   const int64_t s = blockIdx.y;
   float lo = INFINITY, hi = -INFINITY;
   for (int i = threadIdx.x; i < nparts; i += 256) {
@@ -137,9 +135,8 @@ __global__ __launch_bounds__(256) void k_set_encode(const float *__restrict__ X,
   const float2 mm = block_minmax(lo, hi);
   const QParams p = make_qparams(mm.x, mm.y);
   if (blockIdx.x == 0 && threadIdx.x == 0) put_set_params(p, s, o);
-  const int64_t r0 = (int64_t)blockIdx.x * kEncodeRows;
-  encode_set_rows(X, s * rps + r0, s * rps + (r0 + kEncodeRows < rps ? r0 + kEncodeRows : rps), cols,
-                  p, o);
+  const int64_t r0 = (int64_t)blockIdx.x * brows;
+  encode_set_rows(X, s * rps + r0, s * rps + (r0 + brows < rps ? r0 + brows : rps), cols, p, o);
 }
 
 // Small sets, one block each: range, params and codes in one launch (the
@@ -262,8 +259,12 @@ hipError_t launch_set_quantize(const float *X, int64_t rows, int64_t cols, int n
   const int parts = set_parts(n);
   const int64_t per = round_up((n + parts - 1) / parts, 4);
   hipLaunchKernelGGL(k_set_minmax, dim3(parts, nsets), dim3(256), 0, s, X, n, per, part);
-  hipLaunchKernelGGL(k_set_encode, dim3(blocks_for(rps, kEncodeRows), nsets), dim3(256), 0, s, X,
-                     rps, cols, part, parts, o);
+  // rows of a block of the encoder: 16, so that its reduction of the partials is
+  // a small part, or one per wave where that leaves the chip idle (16 x 100000, us:
+  // 593 with 16, 123 with 4)
+  const int brows = (rps + 15) / 16 * nsets >= 256 ? 16 : 4;
+  hipLaunchKernelGGL(k_set_encode, dim3(blocks_for(rps, brows), nsets), dim3(256), 0, s, X, rps, cols,
+                     part, parts, brows, o);
   return hipGetLastError();
 }
 
