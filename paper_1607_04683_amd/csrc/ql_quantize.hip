@@ -153,11 +153,11 @@ __global__ __launch_bounds__(1024) void k_set_small(const float *__restrict__ X,
 
 // Recovery (eq. 3), one wave per row: four codes per lane and load where the
 // rows of both sides are aligned for it.
-__global__ __launch_bounds__(256) void k_dequantize(const int8_t *__restrict__ codes, int64_t ld,
-                                                    int64_t rows, int64_t cols, int64_t rpb,
-                                                    const int32_t *__restrict__ zero,
-                                                    const float *__restrict__ inv_q,
-                                                    float *__restrict__ dst, int vec) {
+__global__ __launch_bounds__(256) void k_dequantize_rows(const int8_t *__restrict__ codes, int64_t ld,
+                                                         int64_t rows, int64_t cols, int64_t rpb,
+                                                         const int32_t *__restrict__ zero,
+                                                         const float *__restrict__ inv_q,
+                                                         float *__restrict__ dst, int vec) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
   if (r >= rows) return;
@@ -180,6 +180,34 @@ __global__ __launch_bounds__(256) void k_dequantize(const int8_t *__restrict__ c
     done = cols / 4 * 4;
   }
   for (int64_t i = done + lane; i < cols; i += kWave) d[i] = (float)((int)c[i] + z) * iq;
+}
+
+// The same, W values of a row per thread (4 where the rows of both sides are
+// aligned for it, else 1), the matrix taken as one run of n of them, so that any
+// shape fills the chip.
+template <int W>
+__global__ __launch_bounds__(256) void k_dequantize(const int8_t *__restrict__ codes, int64_t ld,
+                                                    uint32_t n, uint32_t per_row, uint32_t rpb,
+                                                    const int32_t *__restrict__ zero,
+                                                    const float *__restrict__ inv_q,
+                                                    float *__restrict__ dst) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t r = i / per_row, c = i - r * per_row, b = r / rpb;
+  const int z = zero[b] + 128;  // V' = code + 128
+  const float iq = inv_q[b];
+  const int8_t *src = codes + (int64_t)r * ld + (int64_t)W * c;
+  if constexpr (W == 4) {
+    const uint32_t w = *reinterpret_cast<const uint32_t *>(src);
+    float4 v;
+    v.x = (float)((int)(int8_t)w + z) * iq;
+    v.y = (float)((int)(int8_t)(w >> 8) + z) * iq;
+    v.z = (float)((int)(int8_t)(w >> 16) + z) * iq;
+    v.w = (float)((int)(int8_t)(w >> 24) + z) * iq;
+    reinterpret_cast<float4 *>(dst)[i] = v;
+  } else {
+    dst[i] = (float)((int)*src + z) * iq;
+  }
 }
 
 // Row sums of 0..255 codes stored in the signed layout.
@@ -273,10 +301,20 @@ hipError_t launch_dequantize(const int8_t *codes, int64_t ld, int64_t rows, int6
                              hipStream_t s) {
   if (rows * cols == 0) return hipSuccess;
   // every row of codes 4-byte aligned, every row of dst 16-byte aligned
-  const int vec = ld % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0 && cols % 4 == 0 &&
-                  reinterpret_cast<uintptr_t>(dst) % 16 == 0;
-  hipLaunchKernelGGL(k_dequantize, dim3(blocks_for(rows, 4)), dim3(256), 0, s, codes, ld, rows, cols,
-                     rows / nblocks, zero, inv_q, dst, vec);
+  const bool vec = ld % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0 && cols % 4 == 0 &&
+                   reinterpret_cast<uintptr_t>(dst) % 16 == 0;
+  // a wave per row where that fills the chip: no division (us, by rows and by
+  // threads: 16384 x 8192 134 and 157, 16383 x 8191 237 and 374, 16 x 33024 30 and
+  // 6.4, 1 x 1000000 723 and 6.8, 1000000 x 1 107 and 11, 100000 x 40 13 and 6.3),
+  // and where 32 bits do not count the threads
+  const int64_t per_row = vec ? cols / 4 : cols, n = rows * per_row;
+  if ((rows >= 1024 && cols >= 256) || n > (int64_t)UINT32_MAX - 255)
+    hipLaunchKernelGGL(k_dequantize_rows, dim3(blocks_for(rows, 4)), dim3(256), 0, s, codes, ld, rows, cols,
+                       rows / nblocks, zero, inv_q, dst, (int)vec);
+  else
+    hipLaunchKernelGGL((vec ? k_dequantize<4> : k_dequantize<1>), dim3(blocks_for(n, 256)), dim3(256), 0, s,
+                       codes, ld, (uint32_t)n, (uint32_t)per_row, (uint32_t)(rows / nblocks), zero, inv_q,
+                       dst);
   return hipGetLastError();
 }
 

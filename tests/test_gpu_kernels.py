@@ -217,12 +217,19 @@ def test_quantize_activations_per_vector(ql, orc, m, cols):
 
 # Edges of the set quantizer's launches: one block per set up to 8192 values,
 # two launches beyond, up to 65536 a block with 256 sets or more; sets that
-# start off a 16-byte boundary; more than 512 slices of 8192 values; rows around the
-# 512 values the encoder has in flight, with a ragged last block.
+# start off a 16-byte boundary; more than 512 slices of 8192 values; rows around 512
+# and 1024 values, with a ragged last block.
 @pytest.mark.parametrize("rows,cols,nblocks", [(64, 128, 1), (1, 8193, 1), (3, 8191, 3), (9, 2731, 3),
                                                (512, 65, 512), (512, 257, 256), (30, 4097, 2),
                                                (8300, 511, 1), (40, 1030, 1),
-                                               (68, 516, 4), (33, 508, 1), (70, 1028, 1), (3, 4104, 1)])
+                                               (68, 516, 4), (33, 508, 1), (70, 1028, 1), (3, 4104, 1),
+                                               # 4 and 16 rows a block of the encoder: 255 and
+                                               # 256 blocks of 16
+                                               (4080, 12, 1), (4081, 12, 1), (4080, 33, 4),
+                                               # recovery by threads and by rows: 1024 rows
+                                               # of 256, less of either, odd widths
+                                               (1024, 256, 4), (1023, 256, 3), (1024, 255, 2),
+                                               (1030, 257, 1), (5, 1, 5), (2000, 3, 4), (1, 70001, 1)])
 def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
     test_quantize_matches_oracle(ql, orc, rows, cols, nblocks)
 
