@@ -259,11 +259,16 @@ hipError_t launch_quantize_stacked(const float *frames, int64_t B, int dim, int 
 static int set_parts(int64_t setsize) {
   return (int)std::min<int64_t>(kSetParts, std::max<int64_t>(1, (setsize + 8191) / 8192));
 }
-// Sets that one block takes whole: up to 8192 values, one round of its loads.
-// Beyond (more where there are many sets to fill the chip with blocks), two
-// launches over all CUs beat one block's passes.
-static bool set_is_small(int64_t setsize, int64_t nsets) {
-  return setsize <= 8192 || (setsize <= 65536 && nsets >= 256);
+// Threads of the block that takes a set whole; 0: two launches over all CUs beat
+// one block's passes.  Up to 8192 values, one round of its loads (more where there
+// are many sets to fill the chip with blocks), in at most 16 rows a wave, which
+// encodes them one after the other (one set of 4 columns, us, two launches and one
+// block: 256 rows 17.5 and 14.7, 512 17.2 and 26.2, 1024 17.5 and 49; 256 sets of
+// 256 x 16 18.4 and 31).
+static int set_small_threads(int64_t rps, int64_t setsize, int64_t nsets) {
+  const int threads = setsize <= 4096 && nsets > 1 ? 256 : 1024;
+  const bool few = setsize <= 8192 || (setsize <= 65536 && nsets >= 256);
+  return few && rps <= threads / kWave * 16 ? threads : 0;
 }
 
 size_t set_quantize_ws(int64_t rows, int64_t cols, int nsets) {
@@ -278,9 +283,9 @@ hipError_t launch_set_quantize(const float *X, int64_t rows, int64_t cols, int n
   if (rows == 0) return hipSuccess;
   const SetOut o{codes, ld, range, zero, inv_q, row_sums, row_zero, row_inv_q};
   const int64_t rps = rows / nsets, n = rps * cols;
-  if (set_is_small(n, nsets)) {
-    hipLaunchKernelGGL(k_set_small, dim3(nsets), dim3(n <= 4096 && nsets > 1 ? 256 : 1024), 0, s, X,
-                       rps, cols, o);
+  const int small = n == 0 ? 1024 : set_small_threads(rps, n, nsets);
+  if (small) {
+    hipLaunchKernelGGL(k_set_small, dim3(nsets), dim3(small), 0, s, X, rps, cols, o);
     return hipGetLastError();
   }
   float2 *part = static_cast<float2 *>(ws);

@@ -215,14 +215,16 @@ def test_quantize_activations_per_vector(ql, orc, m, cols):
     assert (q.codes[:, cols:] == 0).all()
 
 
-# Edges of the set quantizer's launches: one block per set up to 8192 values,
-# two launches beyond, up to 65536 a block with 256 sets or more; sets that
+# Edges of the set quantizer's launches: one block per set up to 8192 values (and
+# 256 rows, 64 of smaller blocks), two launches beyond, up to 65536 a block with 256 sets or more; sets that
 # start off a 16-byte boundary; more than 512 slices of 8192 values; rows around 512
 # and 1024 values, with a ragged last block.
 @pytest.mark.parametrize("rows,cols,nblocks", [(64, 128, 1), (1, 8193, 1), (3, 8191, 3), (9, 2731, 3),
                                                (512, 65, 512), (512, 257, 256), (30, 4097, 2),
                                                (8300, 511, 1), (40, 1030, 1),
                                                (68, 516, 4), (33, 508, 1), (70, 1028, 1), (3, 4104, 1),
+                                               (256, 3, 1), (257, 3, 1), (256, 16, 4), (260, 16, 4),
+                                               (2056, 4, 1),
                                                # 4 and 16 rows a block of the encoder: 255 and
                                                # 256 blocks of 16
                                                (4080, 12, 1), (4081, 12, 1), (4080, 33, 4),
