@@ -820,8 +820,8 @@ constexpr int kSmallValues = 8192;
 static bool small_product(const float *X, bool per_row, int64_t M, int64_t N, int64_t K) {
   if (M < 1 || N < 1 || M * K > kSmallValues) return false;
   if (K % 4 != 0 || ((uintptr_t)X & 15) != 0) {
-    if (!per_row) return M <= 24;
-    return M <= 4 || (M <= 16 && (M * K <= 4096 || N > 32768));
+    if (!per_row) return M <= 24 || (M <= 32 && M * K <= 4096);
+    return M <= 4 || (M <= 24 && M * K <= 4096) || (M <= 16 && N > 32768);
   }
   return M <= (per_row ? 24 : 32) || (M <= (per_row ? 32 : 64) && N <= 32768);
 }

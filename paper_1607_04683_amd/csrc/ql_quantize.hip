@@ -310,10 +310,10 @@ hipError_t launch_dequantize(const int8_t *codes, int64_t ld, int64_t rows, int6
                    reinterpret_cast<uintptr_t>(dst) % 16 == 0;
   // a wave per row where that fills the chip: no division (us, by rows and by
   // threads: 16384 x 8192 134 and 157, 16383 x 8191 237 and 374, 16 x 33024 30 and
-  // 6.4, 1 x 1000000 723 and 6.8, 1000000 x 1 107 and 11, 100000 x 40 13 and 6.3),
-  // and where 32 bits do not count the threads
+  // 6.4, 1 x 1000000 723 and 6.8, 1000000 x 1 107 and 11, 100000 x 40 13 and 6.3,
+  // 273607 x 175 57 and 76), and where 32 bits do not count the threads
   const int64_t per_row = vec ? cols / 4 : cols, n = rows * per_row;
-  if ((rows >= 1024 && cols >= 256) || n > (int64_t)UINT32_MAX - 255)
+  if ((rows >= 1024 && cols >= (vec ? 256 : 128)) || n > (int64_t)UINT32_MAX - 255)
     hipLaunchKernelGGL(k_dequantize_rows, dim3(blocks_for(rows, 4)), dim3(256), 0, s, codes, ld, rows, cols,
                        rows / nblocks, zero, inv_q, dst, (int)vec);
   else

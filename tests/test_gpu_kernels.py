@@ -228,9 +228,10 @@ def test_quantize_activations_per_vector(ql, orc, m, cols):
                                                # 4 and 16 rows a block of the encoder: 255 and
                                                # 256 blocks of 16
                                                (4080, 12, 1), (4081, 12, 1), (4080, 33, 4),
-                                               # recovery by threads and by rows: 1024 rows
-                                               # of 256, less of either, odd widths
-                                               (1024, 256, 4), (1023, 256, 3), (1024, 255, 2),
+                                               # recovery by threads and by rows: 1024 rows of
+                                               # 256, of 128 off the 16 bytes, less of either
+                                               (1024, 256, 4), (1023, 256, 3), (1024, 252, 2),
+                                               (1024, 129, 1), (1024, 127, 1),
                                                (1030, 257, 1), (5, 1, 5), (2000, 3, 4), (1, 70001, 1)])
 def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
     test_quantize_matches_oracle(ql, orc, rows, cols, nblocks)
@@ -243,7 +244,7 @@ def test_quantize_launch_edges(ql, orc, rows, cols, nblocks):
                                          # one launch up to 8192 values: 16, 24, 32 and 64
                                          # rows of X, aligned and not
                                          (64, 100, 128), (64, 65, 129), (1, 300, 8192), (1, 17, 8193),
-                                         (17, 129, 481), (32, 64, 255), (24, 65, 340), (25, 65, 325),
+                                         (17, 129, 481), (32, 64, 255), (24, 65, 340), (24, 66, 170), (24, 66, 171), (25, 65, 325),
                                          (32, 70, 256), (33, 70, 248), (16, 40, 255), (16, 40, 257),
                                          (24, 32772, 64), (25, 32772, 64), (40, 32768, 64)])
 @pytest.mark.parametrize("gran", [0, 1])
