@@ -35,10 +35,10 @@ FP32_PEAK_TFLOPS = 157.3   # MI355X dense fp32 (MFMA)
 # --pmc passes (FETCH_SIZE, WRITE_SIZE) scaled by the same counters on a plain
 # 1 GiB copy; valid only for the kernel sources with this digest (any edit
 # makes it stale -> null).
-TRAFFIC = dict(bytes=3.7402e+08, read=2.0048e+08, written=1.7355e+08,
+TRAFFIC = dict(bytes=3.7446e+08, read=2.0091e+08, written=1.7355e+08,
                sources=("ql_stack.hip", "ql_xstack.hip", "ql_xcd.h", "ql_rec_common.h",
                         "ql_device.h", "ql_exchange.h", "ql_launch.h"),
-               sha256="900d69aa41da900e2549377d78e4727fdb7388e004564faf5114bdc9feef0a4f",
+               sha256="6c6a6ed0bf48619d08bfc4befea6dd908bad03b13f48fd49e2b55861a528c2fc",
                summary="profiles/k_xstack_5x500_B64_T1000_counters.md")
 
 

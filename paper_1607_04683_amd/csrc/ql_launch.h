@@ -211,7 +211,7 @@ hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s,
 // The same on the whole chip as independent row groups of 16 workgroups each
 // (ql_xstack.hip), over as many launches as the batch needs; ws_bytes of a.ws
 // may be used.  *done false when the shapes or the device do not fit that
-// layout (nothing launched).
+// layout (nothing launched; launch_stack_chip decides whether it pays).
 size_t xstack_ws(int nl);
 bool xstack_applies(const StackArgs &a, size_t ws_bytes, int cus, int lds_max);
 // One batch row on the whole chip (ql_xrow.hip): one XCD per layer.  *done as above.
@@ -276,7 +276,7 @@ size_t recurrent_f32_ws(int64_t B, int64_t H, int64_t P);
 hipError_t launch_recurrent_f32(const F32RecArgs &a, hipStream_t s, bool *unsupported);
 // Layers without a projection on the whole chip (ql_xf32.hip): each XCD runs
 // an eighth of the batch.  *done false when the shapes or the device do not
-// fit that layout (nothing launched).
+// fit that layout, or another is faster (nothing launched).
 hipError_t launch_xrec_f32(const F32RecArgs &a, int cus, int lds_max, hipStream_t s, bool *done);
 // How many launches that layout takes such a layer in; 0: none.
 int xrec_f32_launches(int64_t H, int64_t T, int64_t B, int cus, int lds_max);

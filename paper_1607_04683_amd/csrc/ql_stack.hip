@@ -26,8 +26,9 @@
 // the tagged h words until every tag matches, quantize, store the codes with
 // device-coherent stores and then bump the slice's arrival counter, which
 // the unit tiles and the next layer wait on.
-// This is the layout of a partition of the chip and of wider inputs; the whole
-// chip runs one row in ql_xrow.hip, a few in ql_xrows.hip and more in ql_xstack.hip.
+// This is the layout of a partition of the chip, of wider inputs, and of batches
+// of narrow layers that would take several launches elsewhere; the whole chip runs
+// one row in ql_xrow.hip, a few in ql_xrows.hip and more in ql_xstack.hip.
 //
 // Between layers nothing is reused: codes go to full-length [T*B] buffers,
 // so a layer may run any number of steps ahead of the next one; a layer

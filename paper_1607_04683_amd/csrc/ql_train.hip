@@ -158,8 +158,9 @@ hipError_t launch_sgd(float *w, const float *g, int64_t n, float lr, hipStream_t
 // added in wave order (the result does not depend on timing); then the
 // cell's backward step and its part of da_t.  Counters are per step, so
 // nothing is reused in a launch.
-// This is the layout of a partition of the chip; the whole chip runs the
-// recurrence with an eighth of the batch per XCD (ql_xbptt.hip).
+// This is the layout of a partition of the chip and of batches that would take
+// several launches that do not pay; the whole chip runs the recurrence with an
+// eighth of the batch per XCD (ql_xbptt.hip).
 // ---------------------------------------------------------------------------
 constexpr int kBpttThreads = 512;
 constexpr int kBpttWaves = kBpttThreads / 64;

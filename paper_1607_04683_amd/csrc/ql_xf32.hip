@@ -23,7 +23,7 @@
 // h_{t-1}.  Bound by the latency of that chain: one hand-off through L2 (about
 // 1 us) and 128 dependent-issue MFMAs a wave (0.85 us at 8 rows).
 // Five 500-cell layers at batch 64: 13.7 us a step of one layer in the layout
-// with a tile of the batch per workgroup and device-coherent counters, 3.6 us
+// with a tile of the batch per workgroup and device-coherent counters, 3.25 us
 // here.
 #include "ql_device.h"
 #include "ql_exchange.h"

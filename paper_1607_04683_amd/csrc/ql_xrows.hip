@@ -3,10 +3,10 @@
 // (ql_xrow.hip) for up to eight rows, one persistent launch over the whole
 // chip, one XCD per layer and row group, run as a wavefront.
 //
-// A row group is up to NR rows (4, or 8 with a projection); n layers leave room for floor(8 / n)
-// groups a launch, and larger batches take several launches.  Up to 32
-// workgroups of an XCD own 16 cells of the layer each, and 16 outputs of its
-// projection.  Waves 0-3 carry the chain from h_{t-1} to h_t: NR / 4 rows each,
+// A row group is up to NR rows (4, or 8 with a projection); n layers leave room for
+// floor(8 / n) groups a launch, and larger batches with projections take several
+// launches where those pay.  Up to 32 workgroups of an XCD own 16 cells of the
+// layer each, and 16 outputs of its projection.  Waves 0-3 carry the chain from h_{t-1} to h_t: NR / 4 rows each,
 // 64 values an instruction, polled in tagged words through the XCD's L2,
 // quantized in the wave (eq. 2), the codes to LDS, one barrier; then the 64 gate
 // rows of W_h' times the codes, rows in the columns of the MFMA.  The rows

@@ -7,9 +7,9 @@
 // reads its XCC_ID and takes the next free slot of its XCD) of 32 cells each,
 // or on 8 workgroups of 64 cells.  The chip holds 16 or 32 units, so n layers
 // take floor(16 / n) or floor(32 / n) row groups a launch (5 layers: 48 or 96
-// rows), and larger batches several launches.  Every hand-off inside a unit
-// stays in that XCD's L2: plain stores, device-coherent loads that find them
-// there.  What bounds a step is the latency of two such hand-offs (about 1 us
+// rows), and larger batches several launches where those pay (ql_stack.hip says
+// when).  Every hand-off inside a unit stays in that XCD's L2: plain stores,
+// device-coherent loads that find them there.  What bounds a step is the latency of two such hand-offs (about 1 us
 // each) and of the phases between them; 64-cell tiles add their second cells'
 // arithmetic.  A frame through 5 x 500 cells (200 frames, start-up included),
 // us: 16 rows 4.3, 48 rows 4.6, 64 rows 5.6, 96 rows 5.9, 150 rows (two
