@@ -388,6 +388,20 @@ bool stackable(const ql_model &M) {
   }
   return true;
 }
+// Layers of the launch that takes on the layers from l on of a stackable model:
+// nearly equal shares of what is left, of a size that a launch takes (a share may
+// be one that the layout of a larger one does not take).
+int stack_group(const ql_model &M, int l, int64_t T, int64_t B) {
+  const int64_t H = M.layers[0].hidden;
+  int n = M.nlayers - l;
+  while (n > 1) {
+    const int per = stack_layers_routed(n, T, B, H, M.layers[l].in, H);
+    if (per >= n) break;
+    const int launches = (n + per - 1) / per;
+    n = (n + launches - 1) / launches;
+  }
+  return n;
+}
 // Initial / final state of layer l of a call (host arrays of per-layer
 // descriptors, each nullable).
 const float *st_h(const ql_lstm_state *s, int l) { return s ? s[l].h : nullptr; }
@@ -643,13 +657,7 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
   ActRows cur = mw.xin.rows();
   const bool stack = stackable(*M);
   const bool pst = !stack && pstack_shapes(M->layers, M->nlayers, B);
-  int per_launch = 1;
-  if (stack) {
-    const int64_t in1 = M->nlayers > 1 ? M->layers[1].in : M->layers[0].in;
-    per_launch = stack_layers_routed(M->nlayers, T, B, maxH, M->layers[0].in, in1);
-  } else if (pst) {
-    per_launch = pstack_per_launch(M->layers, M->nlayers, T, B);
-  }
+  const int per_launch = pst ? pstack_per_launch(M->layers, M->nlayers, T, B) : 1;
   bool whole = false;
   if (!stack && !pst) {
     ActBuf last = mw.out[0];
@@ -663,7 +671,7 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
     const int left = M->nlayers - l;
     // split the layers into launches of nearly equal size
     const int launches = (left + per_launch - 1) / per_launch;
-    const int n = (left + launches - 1) / launches;
+    const int n = stack ? stack_group(*M, l, T, B) : (left + launches - 1) / launches;
     if (stack && n >= 2) {
       StackArgs sa{};
       sa.nl = n;
@@ -1116,9 +1124,8 @@ int32_t ql_debug_model_layout(const ql_model *M, int64_t T, int64_t B, int32_t *
     if (nr) nlaunch = k;
     return nr == 0 ? kPathLayers : nr == 4 ? kPathXrows4 : kPathXrows8;
   }
-  const int per = stack ? stack_layers_routed(n_all, T, B, maxH, M->layers[0].in, M->layers[1].in)
-                        : pstack_per_launch(M->layers, n_all, T, B);
-  const int groups = (n_all + per - 1) / per, n = (n_all + groups - 1) / groups;
+  const int per = pst ? pstack_per_launch(M->layers, n_all, T, B) : 1, groups = (n_all + per - 1) / per;
+  const int n = stack ? stack_group(*M, 0, T, B) : (n_all + groups - 1) / groups;
   if (n < 2) return kPathLayers;
   nlaunch = 1;
   auto out = [&](int l) {
