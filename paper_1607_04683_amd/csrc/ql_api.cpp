@@ -509,13 +509,17 @@ ql_status run_proj_rows(const ql_model &M, const ActRows &xin, const ActBuf &las
 
 // Workspace of a model forward: exchange scratch first (it holds the timeout
 // flag), then the input codes, W_x x + b, one code buffer per layer, h.
+// (a launch of up to kMaxStack layers reads the layer before's and writes its own)
+constexpr int kOutBufs = 16;
+static_assert(kOutBufs > kMaxStack, "output buffers of a launch");
 struct ModelWs {
   void *rec;
   ActBuf xin;
   float *gx;
-  ActBuf out[kMaxStack > 16 ? kMaxStack : 16];
+  ActBuf out[kOutBufs];
   float *hf;
   void *sws;
+  const ActBuf &out_of(int l) const { return out[l % kOutBufs]; }  // layer l, layers in launches
 };
 ModelWs carve_model(Carve &c, const ql_model &M, int64_t T, int64_t B) {
   int64_t maxH = 0, maxR = 0, maxP = 0;
@@ -544,7 +548,7 @@ ModelWs carve_model(Carve &c, const ql_model &M, int64_t T, int64_t B) {
   w.xin = take_act(c, MB, M.layers[0].in);
   w.gx = c.take<float>((size_t)(MB * 4 * maxH));
   // one output code buffer per layer (two alternate when layers run one by one)
-  const int nbuf = stackable(M) || pst ? (M.nlayers < 16 ? M.nlayers : 16) : 2;
+  const int nbuf = stackable(M) || pst ? std::min(M.nlayers, kOutBufs) : 2;
   for (int i = 0; i < nbuf; ++i) w.out[i] = take_act(c, MB, maxR);
   w.hf = c.take<float>((size_t)(MB * maxR));
   w.sws = c.take<char>(softmax_ws(MB, M.Wy.rows));
@@ -681,13 +685,13 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
       sa.ws = mw.rec;
       for (int k = 0; k < n; ++k) {
         const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l + k] : nullptr;
-        const ActRows xin = k == 0 ? cur : mw.out[l + k - 1].rows();
-        sa.L[k] = stack_layer(M->layers[l + k], xin, mw.out[l + k], lt, s0, s1, l + k);
+        const ActRows xin = k == 0 ? cur : mw.out_of(l + k - 1).rows();
+        sa.L[k] = stack_layer(M->layers[l + k], xin, mw.out_of(l + k), lt, s0, s1, l + k);
       }
       bool unsupported = false;
       if (launch_stack(sa, s, &unsupported) != hipSuccess) return QL_EHIP;
       if (unsupported) return QL_EUNSUPPORTED;
-      cur = mw.out[l + n - 1].rows();
+      cur = mw.out_of(l + n - 1).rows();
       l += n;
       continue;
     }
@@ -699,13 +703,13 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
       pa.ws = mw.rec;
       for (int k = 0; k < n; ++k) {
         const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l + k] : nullptr;
-        pa.L[k] = pstack_layer(M->layers[l + k], k == 0 ? cur : ActRows{}, mw.out[l + k], lt, s0,
+        pa.L[k] = pstack_layer(M->layers[l + k], k == 0 ? cur : ActRows{}, mw.out_of(l + k), lt, s0,
                                s1, l + k);
       }
       bool unsupported = false;
       if (launch_pstack(pa, s, &unsupported) != hipSuccess) return QL_EHIP;
       if (unsupported) return QL_EUNSUPPORTED;
-      cur = mw.out[l + n - 1].rows();
+      cur = mw.out_of(l + n - 1).rows();
       l += n;
       continue;
     }
@@ -713,7 +717,7 @@ ql_status model_forward(const ql_model *M, const Frontend &fe, int64_t T, int64_
     LayerWs w;
     w.rec = mw.rec;
     w.gx = mw.gx;
-    w.hout = mw.out[stack || pst ? l : (l & 1)];
+    w.hout = stack || pst ? mw.out_of(l) : mw.out[l & 1];
     w.hout.ld = round_up(layer_width(L), 64);
     const ql_lstm_taps *lt = taps && taps->layers ? &taps->layers[l] : nullptr;
     st = run_layer(L, cur, T, B, st_h(s0, l), st_c(s0, l), lt && lt->h ? lt->h : mw.hf,

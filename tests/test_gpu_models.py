@@ -345,3 +345,17 @@ def test_model_5x500_stream_chunks_T500_B1(ql):
     assert torch.equal(post, full["post"])
     for l in range(5):
         assert torch.equal(codes[l], full["layers"][l]["h_codes"]), l
+
+
+# More layers than the model's workspace has output buffers for (16): the buffers
+# of a launch's layers are used again two launches later.
+@pytest.mark.parametrize("layers,H,P,T,B", [(16, 16, 0, 3, 1), (17, 16, 0, 3, 1), (17, 16, 8, 3, 1),
+                                            (20, 24, 0, 2, 3), (33, 16, 0, 2, 20), (17, 16, 0, 1, 1000),
+                                            (17, 16, 8, 2, 3)])
+def test_deep_models_equal_oracle(ql, orc, layers, H, P, T, B):
+    from paper_1607_04683_amd.workloads import random_model
+    w = random_model(24, H, layers, proj=P, states=24, seed=layers + B)
+    x = np.random.default_rng(layers).standard_normal((T, B, 24)).astype(np.float32)
+    g = ql.acoustic_model_forward(ql.quantize_model(w), torch.from_numpy(x).cuda(), taps=True)
+    o = orc.acoustic_model_forward(orc.quantize_model(w), x, taps=True)
+    assert_model_taps(g, o, None, names=ql.TAP_NAMES)
