@@ -38,7 +38,7 @@ FP32_PEAK_TFLOPS = 157.3   # MI355X dense fp32 (MFMA)
 TRAFFIC = dict(bytes=3.7446e+08, read=2.0091e+08, written=1.7355e+08,
                sources=("ql_stack.hip", "ql_xstack.hip", "ql_xcd.h", "ql_rec_common.h",
                         "ql_device.h", "ql_exchange.h", "ql_launch.h"),
-               sha256="6c6a6ed0bf48619d08bfc4befea6dd908bad03b13f48fd49e2b55861a528c2fc",
+               sha256="199c614eae8da253bea7bb0ffac7cfe1b028bdcb17d98d078b7361304b6e5680",
                summary="profiles/k_xstack_5x500_B64_T1000_counters.md")
 
 

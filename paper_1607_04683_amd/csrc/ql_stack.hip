@@ -956,20 +956,21 @@ static bool chip_takes_batch(const StackArgs &a, int cus, int lds_max) {
 // a frame against 5.5 and more).  Several are a matter of widths: a unit's step
 // costs the same at 16 cells as at 512, where the tiles of the other kernels hold
 // more rows the narrower they are.  us, from runs of 1 to 8 layers of 16 to 500
-// cells, 65 to 1000 rows, 5 and 50 frames (the rule takes the slower side by at
-// most 4% there):
+// cells, 65 to 1000 rows, 5 and 50 frames (where it takes the units, they are the
+// faster side of every one):
 //   units          per launch 17 + 15.5 a layer (filling the wavefront) + 4.8 a frame
-//   other kernels  per launch 50 + the step's time below a frame
+//   other kernels  per launch 50 + the step's time below a frame; several layers
+//                  30 + 5 a layer once
 // 5 layers, 50 frames, units and other: 500 cells, 300 rows (4 launches, a launch
-// per layer) 1415 and 3300; 100 cells, 300 rows (4 launches and 2) 1407 and 860.
+// per layer) 1422 and 3697; 100 cells, 300 rows (4 launches and 2) 1400 and 887.
 static bool units_pay(const StackArgs &a, int launches) {
   if (launches <= 1) return true;
   const int per = a.nl > 1 ? stack_layers_per_launch(a.nl, a.T, a.B, a.H, a.L[0].in, a.L[1].in) : 1;
   const int others = (a.nl + per - 1) / per;
   const double T = (double)a.T, H = (double)a.H, HB = H * (double)a.B;
   const double step = per > 1 ? 5.0 + 0.003 * H + 1.5e-5 * HB : 7.0 + 0.004 * H + 2.5e-5 * HB;
-  return launches * (17.0 + 15.5 * a.nl + 4.8 * T) - 40.0 <=
-         others * (50.0 + step * T) + (a.nl > 1 ? 5.0 * a.nl : -40.0);
+  return launches * (17.0 + 15.5 * a.nl + 4.8 * T) <=
+         others * (50.0 + step * T) + (a.nl > 1 ? 30.0 + 5.0 * a.nl : 0.0);
 }
 
 hipError_t launch_stack_chip(const StackArgs &a, size_t ws_bytes, hipStream_t s, bool *done) {
