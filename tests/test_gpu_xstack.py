@@ -1,13 +1,13 @@
-"""Stacked layers without a projection (Section 4) at batch 16 to 64 on the
-whole chip run in the XCD-local layer wavefront: XCD l runs layer l for the
-whole sequence, its 32 workgroups (2 row groups x 16 cell tiles) hand the
-codes of h_t and the rows' min / max to each other through the XCD's own L2,
-and each layer's quantized output crosses to the next XCD.  Every tap of
+"""Stacked layers without a projection (Section 4) on the whole chip: units of
+up to 16 batch rows of one layer, on 16 workgroups of 32 cells or 8 of 64 that
+share an XCD, hand the codes of h_t and the rows' min / max to each other through
+its L2, and each layer's quantized output crosses to the next XCD.  Every tap of
 every layer (input and recurrent sums, codes, row params, fp32 h, gates, c)
-is compared with the oracle bit for bit on ragged shapes: the smallest and
-largest batch, odd batches (the second row group one row short), cell counts
-that leave tiles without cells, the widest input and cell count, the most
-layers one launch holds, and sequences of one and two frames."""
+is compared with the oracle bit for bit on ragged shapes: the smallest batch and
+full units, units one row short, cell counts that leave tiles without cells, the
+widest input and cell count, the most layers one launch holds, several launches,
+what other batches fall back to, and sequences of one and two frames; each case
+asserts the kernel that ran."""
 import numpy as np
 import pytest
 import torch
